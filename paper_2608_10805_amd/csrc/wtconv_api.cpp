@@ -7,6 +7,7 @@
 #include <mutex>
 
 #include "wtconv_internal.h"
+#include "wtconv_phase_args.h"
 
 namespace {
 
@@ -1083,6 +1084,266 @@ wtc::TinyArgs tiny_args(const wtconv_desc& d, const void* in, const void* aux, v
     return t;
 }
 
+// ----------------------------------------------------------------------------
+// Polyphase forward on the matrix cores (wtconv_phase_fwd.hip): k = 3 and 5,
+// one to five levels. A plane whose stages fit one CU's LDS runs whole in one
+// launch; a larger one runs its first level in region tiles, with the levels
+// above it as the coarse sub-problem on the level-1 carrier.
+// ----------------------------------------------------------------------------
+struct PhasePlan {
+    wtc::PhaseArgs a;  // geometry, LDS layout, nb and PP (pointers unset)
+    int rounds = 1;    // 4 x 4 block rounds per thread
+    int nchunks = 1;
+};
+
+struct PhaseExec {
+    enum Kind { None, Resident, Region } kind = None;
+    PhasePlan pl;
+};
+
+// Lays out the LDS of PP planes whose stage grids, row segments (V, js) and
+// loaded blocks are set; false if it does not fit.
+bool phase_layout(const wtconv_desc& d, wtc::PhaseArgs& a)
+{
+    constexpr int M = wtc::kPhaseMargin;
+    const int R = d.k / 2;
+    const int nx0 = d.dtype == WTCONV_F32 ? 3 : 1, nw0 = d.dtype == WTCONV_F16 ? 2 : 3;
+    int tab = 0;
+    long off = 0;
+    for (int s = 0; s < std::max(a.L, 1); ++s) {
+        wtc::PhaseStage& g = a.st[s];
+        if (s >= 1) {
+            g.tab = tab;
+            tab += ceil_to(3 * 4 * d.k * wtc::kPhaseTabPitch * 2, 16);
+        }
+        // rows: the zero margin above, the blocks written and the windows read
+        const int cover = s == 0 ? 4 * a.by - (a.rg_ntx > 0 ? M : 0) : (s == 1 ? 2 * a.by : (s == 2 ? a.by : g.h));
+        const int rows = M + std::max(cover, 2 * g.V * g.js + 2 * R);
+        g.pitch = 8 * ((g.ct + 1) | 1);  // odd multiples of 16 bytes spread the rows over the banks
+        g.psz = ceil_to(rows * g.pitch * 2, 16);
+        g.poff = (int)off;
+        off += (long)(s == 0 ? nx0 : 3) * g.psz;
+        if (s >= 1) {
+            g.rpitch = 8 * g.ct;
+            g.roff = (int)off;
+            off += ceil_to(2 * g.V * g.js * g.rpitch * 4, 16);
+        }
+        if (s >= 2 && s + 1 < a.L) {
+            g.mf = (int)off;
+            off += ceil_to(g.h * g.w * 4, 16);
+        }
+        g.r_ct = 1.0f / (float)g.ct;
+        g.r_vct = 1.0f / (float)(g.V * g.ct);
+        if (off > (1L << 24)) return false;
+    }
+    a.mark_off = tab;
+    tab += ceil_to(2 * a.PP * (1 + (a.L == 1 ? 4 : 1) * a.bx * a.by), 16);
+    a.planes_off = tab;
+    a.plane_bytes = (int)off;
+    // stage 0's table and the staged kernels borrow the planes' area
+    const int tab0 = ceil_to(nw0 * 8 * d.k * wtc::kPhaseTabPitch * 2 + (1 + 4 * a.L) * d.k * d.k * 8, 16);
+    const long total = tab + std::max<long>(a.PP * off, tab0);
+    if (total > 160 * 1024) return false;
+    a.lds_bytes = (int)total;
+    a.r_bx = 1.0f / (float)a.bx;
+    a.r_bxy = 1.0f / (float)(a.bx * a.by);
+    return true;
+}
+
+int phase_wgs(const wtconv_desc& d, const wtc::PhaseArgs& a, int rounds)
+{
+    const int regs = d.k == 5 && d.dtype == WTCONV_F32 && rounds == 2 ? 2 : 3;
+    return std::max(1, std::min(regs, lds_wgs(cdiv(a.lds_bytes, 4))));
+}
+
+// Modeled cycles of one batch of a workgroup: the matrix instructions of the
+// longer of the fine and the coarse side (16 cycles each) plus the block
+// conversion, barriers and latencies.
+double phase_cycles(const wtconv_desc& d, const wtc::PhaseArgs& a, int rounds)
+{
+    const int np = d.dtype == WTCONV_F32 ? 6 : (d.dtype == WTCONV_BF16 ? 3 : 2);
+    const double fine = 16.0 * a.st[0].js * d.k * np + 40 * a.st[0].js;
+    double coarse = 0, first = 0;
+    for (int s = 1; s < a.L; ++s) {
+        const wtc::PhaseStage& g = a.st[s];
+        const bool whole = g.h <= 4;  // the plane's own rows alone
+        const double c = cdiv(a.PP * g.V * g.ct, 16) * (16.0 * g.js * (whole ? g.js : d.k) * 6 + (whole ? 300 : 600));
+        if (s == 1 && a.fine_waves == 2)
+            first = c;
+        else
+            coarse += c + (a.L - (a.fine_waves == 2 ? 2 : 1) > 1 ? (whole ? 200 : 700) : 0);
+    }
+    return std::max(fine, std::max(first, coarse)) + 600 * rounds + 600;
+}
+
+// Sets the batch chunks; returns the modeled cycles of the busiest slot.
+double phase_chunks(const wtconv_desc& d, PhasePlan& pp, int tiles)
+{
+    // one round of resident workgroups where the batch allows it
+    const int slots = 256 * phase_wgs(d, pp.a, pp.rounds);
+    const int chunks = std::max(1, std::min(cdiv(d.B, pp.a.PP), slots / std::max(1, d.C * tiles)));
+    pp.a.nb = std::min(ceil_to(cdiv(d.B, chunks), pp.a.PP), 32768 * pp.a.PP);  // batches are numbered in 16 bits
+    pp.nchunks = cdiv(d.B, pp.a.nb);
+    const long grid = (long)pp.nchunks * d.C * tiles;
+    return phase_cycles(d, pp.a, pp.rounds) * (pp.a.nb / pp.a.PP) * ((grid + slots - 1) / slots);
+}
+
+bool make_phase_plan(const wtconv_desc& d, PhasePlan& out)
+{
+    double best = -1;
+    const long HW = (long)d.H * d.W;
+    for (int PP = 1; PP <= std::min(d.B, 32); ++PP)
+      for (int fw = d.L > 1 ? 3 : 4; fw >= (d.L > 2 ? 2 : (d.L > 1 ? 3 : 4)); --fw) {
+        if (((PP - 1L) * d.C + 1) * HW >= 1L << 29) break;  // 32-bit byte offsets within a batch
+        PhasePlan pp;
+        wtc::PhaseArgs& a = pp.a;
+        memset(&a, 0, sizeof(a));
+        a.B = d.B;
+        a.C = d.C;
+        a.H = d.H;
+        a.W = d.W;
+        a.L = d.L;
+        a.PP = PP;
+        a.fine_waves = fw;
+        a.bx = ceil_to(d.W, 4) / 4;
+        a.by = ceil_to(d.H, 4) / 4;
+        const long blocks = (long)PP * a.bx * a.by;
+        if (blocks > 2 * wtc::kThreads) break;
+        pp.rounds = blocks > wtc::kThreads ? 2 : 1;
+        int h = d.H, w = d.W;
+        bool ok = true;
+        for (int s = 0; s < d.L && ok; ++s) {
+            wtc::PhaseStage& g = a.st[s];
+            g.h = h;
+            g.w = w;
+            g.ct = ceil_to(w, 8) / 8;
+            const int jt = (h + 1) / 2;
+            if (s == 0) {
+                g.V = 16 * a.fine_waves / (PP * g.ct);
+                ok = g.V >= 1;
+                if (!ok) break;
+                g.js = cdiv(jt, g.V);
+                g.V = cdiv(jt, g.js);
+                ok = g.js <= wtc::phase_max_js(pp.rounds);
+            } else {
+                double bc = -1;
+                if (jt <= 2) {  // one run per column of tiles, over the plane's own rows
+                    g.js = jt;
+                    g.V = 1;
+                } else for (int js : {1, 2, 4}) {
+                    const int V = cdiv(jt, js);
+                    const double c = cdiv(PP * V * g.ct, 16) * (16.0 * js * d.k * 6 + 200);
+                    if (bc < 0 || c < bc) {
+                        bc = c;
+                        g.js = js;
+                        g.V = V;
+                    }
+                }
+            }
+            h = (h + 1) / 2;
+            w = (w + 1) / 2;
+        }
+        if (!ok || !phase_layout(d, a)) continue;
+        const double score = phase_chunks(d, pp, 1);
+        if (best < 0 || score < best) {
+            best = score;
+            out = pp;
+        }
+    }
+    return best >= 0;
+}
+
+bool make_phase_region_plan(const wtconv_desc& d, PhasePlan& out)
+{
+    double best = -1;
+    for (int ct = 4; ct <= 16; ++ct)
+        for (int js = 2; js <= wtc::phase_max_js(2); ++js) {
+            PhasePlan pp;
+            wtc::PhaseArgs& a = pp.a;
+            memset(&a, 0, sizeof(a));
+            a.B = d.B;
+            a.C = d.C;
+            a.H = d.H;
+            a.W = d.W;
+            a.L = 1;
+            a.PP = 1;
+            a.fine_waves = 4;
+            wtc::PhaseStage& g = a.st[0];
+            g.ct = std::min(ct, cdiv(d.W, 8));
+            g.js = js;
+            g.V = std::min(64 / g.ct, cdiv(d.H, 2 * js));
+            if ((g.V * js) % 2) --g.V;
+            if (g.V < 1) continue;
+            a.rg_tw = 8 * g.ct;
+            a.rg_th = 2 * g.V * js;
+            a.rg_ntx = cdiv(d.W, a.rg_tw);
+            a.rg_nty = cdiv(d.H, a.rg_th);
+            g.h = a.rg_th;
+            g.w = a.rg_tw;
+            a.bx = a.rg_tw / 4 + 2;
+            a.by = a.rg_th / 4 + 2;
+            if (a.bx * a.by > 2 * wtc::kThreads) continue;
+            pp.rounds = 2;
+            if (!phase_layout(d, a)) continue;
+            phase_chunks(d, pp, a.rg_ntx * a.rg_nty);
+            const double score = phase_cycles(d, a, 2) * a.rg_ntx * a.rg_nty / phase_wgs(d, a, 2);
+            if (best < 0 || score < best) {
+                best = score;
+                out = pp;
+            }
+        }
+    return best >= 0;
+}
+
+// Where the polyphase forward is the faster one. Measured on MI355X against the
+// vector kernels (forward time, polyphase / vector; k = 5 and 3):
+//  - 16-bit storage, L <= 4: 0.30 (63 x 95 L1) to 0.99, most shapes 0.45-0.75;
+//    float32, L <= 2: 0.61 (128 x 128 L1) to 1.0, most 0.80-0.95; L = 3
+//    0.69-0.95, but at k = 5 on planes up to 32 pixels 0.98-1.07 (in a training
+//    step 28 x 28 1.04);
+//  - float32, L >= 4: 0.84 to 1.8 (its deeper stages need six products per
+//    term and one wavefront runs them);
+//  - 16-bit, L = 5: 56 x 56 0.88, 28 x 28 0.75, 20 x 20 0.78, but 40 x 40 1.08
+//    and 14 x 14 at 49152 planes, where the split's one-plane-per-lane kernel
+//    has enough planes, 1.12;
+//  - L >= 2 on planes that go one to a batch and leave more than half the
+//    threads without a block (31 x 47): 1.02-1.4;
+//  - a plane too tall for one workgroup's columns runs in region tiles with a
+//    carrier pass; where the vector kernels hold it whole they are faster at
+//    L >= 2 (84 x 84 1.4-1.9), and in float32 at L >= 2 the tiles win on
+//    128 x 128 (0.79-0.90) and 96 x 96 (0.89-0.96), not on 224 x 224 (a
+//    training step 1.01-1.04); at k = 3 it is the other way round (224 x 224
+//    0.95-0.98, 96 x 96 L3 1.11).
+bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
+{
+    if (e.kind == PhaseExec::None) return false;
+    const int edge = std::max(d.H, d.W);
+    if (e.kind == PhaseExec::Region)
+        return choose(d, false).mode == Mode::Region &&
+               (d.dtype != WTCONV_F32 || d.L < 2 || (d.k == 3 ? edge >= 112 : edge <= 160));
+    const wtc::PhaseArgs& a = e.pl.a;
+    if (d.L >= 2 && a.PP == 1 && 2 * a.bx * a.by < wtc::kThreads) return false;
+    if (d.dtype == WTCONV_F32) return d.L <= 2 || (d.L == 3 && (d.k == 3 || edge > 32));
+    if (d.L <= 4) return true;
+    return edge >= 48 || (edge <= 32 && (long)d.B * d.C < kSplitMinPlanes);
+}
+
+// region: always in region tiles (a pass on the first level with a carry).
+PhaseExec choose_phase(const wtconv_desc& d, bool region = false)
+{
+    PhaseExec none;
+    if (!wtc::launch_phase_forward || (d.k != 3 && d.k != 5) || d.L < 1 || d.W < 4 || use_tiny(d)) return none;
+    static PlanCache<PhaseExec> cache;
+    return cache.get(d, region ? 1 : 0, [&] {
+        PhaseExec e;
+        if (!region && d.L <= wtc::kPhaseMaxStages && make_phase_plan(d, e.pl))
+            e.kind = PhaseExec::Resident;
+        else if (make_phase_region_plan(d, e.pl))
+            e.kind = PhaseExec::Region;
+        return region || phase_pays(d, e) ? e : none;
+    });
+}
+
 const size_t kUnsupported = ~(size_t)0;
 
 // Kernel-gradient partials written by the fused (or tiny) pass of `ex`.
@@ -1108,6 +1369,12 @@ size_t pass_partial_bytes(const wtconv_desc& d, const Exec& ex)
 //   backward: [partials][X_m][dY_m][dX_m][sub-problem]
 size_t forward_ws(const wtconv_desc& d)
 {
+    const PhaseExec pe = choose_phase(d);
+    if (pe.kind != PhaseExec::None) {
+        if (pe.kind == PhaseExec::Resident || d.L < 2) return 0;
+        const size_t sub = forward_ws(coarse_desc(d, 1));
+        return sub == kUnsupported ? sub : 2 * level_bytes(d, 1) + sub;
+    }
     const Exec ex = choose(d, false);
     if (ex.mode == Mode::None) return kUnsupported;
     if (!ex.coarse) return 0;
@@ -1302,9 +1569,56 @@ void attach_fin(FusedArgs& a, int& grid, FinJob* fin)
     fin->done = true;
 }
 
+// The polyphase pass `pe` of d (region mode: its first level alone, with the
+// levels above it, if any, as `carry` on the level-1 grid).
+wtconv_status phase_pass(const wtconv_desc& d, const PhaseExec& pe, const void* in, const wtc::ParamPtrs& p, void* out,
+                         int skip_base, const void* carry, hipStream_t stream, FinJob* fin)
+{
+    wtc::PhaseArgs a = pe.pl.a;
+    a.in = in;
+    a.out = out;
+    a.p = p;
+    a.skip_base = skip_base;
+    if (carry) {
+        const wtconv_desc c = coarse_desc(d, 1);
+        a.carry = carry;
+        a.carry_H = c.H;
+        a.carry_W = c.W;
+    }
+    int grid = pe.pl.nchunks * d.C * (pe.kind == PhaseExec::Region ? a.rg_ntx * a.rg_nty : 1);
+    if (fin) {
+        a.fin = fin->r;
+        // a grid that leaves CUs free takes workgroups of their own for the
+        // finalize; one that fills its round of slots runs it on the way
+        // (workgroups at its head would push plane workgroups to a second
+        // round: 56 x 56 B64 C96 L3 dx +4 us)
+        const int blocks = ceil_to(cdiv((long)fin->r.C * (1 + 4 * fin->r.L), 4), 8);
+        if (grid + blocks <= 256 * phase_wgs(d, a, pe.pl.rounds))
+            a.fin_blocks = blocks;
+        else
+            a.fin_tasks = fin->r.C * (1 + 4 * fin->r.L);
+        grid += a.fin_blocks;
+        fin->done = true;
+    }
+    return hip_status(wtc::launch_phase_forward(d.k, d.dtype, a, grid, pe.pl.rounds, stream));
+}
+
 wtconv_status forward_impl(const wtconv_desc& d, const void* x, const wtc::ParamPtrs& p, void* y, char* ws,
                            int skip_base, hipStream_t stream, FinJob* fin = nullptr)
 {
+    const PhaseExec pe = choose_phase(d);
+    if (pe.kind != PhaseExec::None) {
+        const void* carry = nullptr;
+        if (pe.kind == PhaseExec::Region && d.L >= 2) {
+            const size_t n1 = level_bytes(d, 1);
+            wtconv_status st = carrier(d, 1, x, ws, stream);
+            if (st == WTCONV_OK)
+                st = forward_impl(coarse_desc(d, 1), ws, shift_params(p, 1), ws + n1, ws + 2 * n1, 1, stream);
+            if (st != WTCONV_OK) return st;
+            carry = ws + n1;
+        }
+        return phase_pass(d, pe, x, p, y, skip_base, carry, stream, fin);
+    }
     const Exec ex = choose(d, false);
     if (ex.mode == Mode::None) return WTCONV_ERR_UNSUPPORTED;
     if (ex.mode == Mode::Tiny)
@@ -1441,6 +1755,8 @@ wtconv_status region_grad_backward(const wtconv_desc& d, const Exec& ex, const G
     pr.b0 = nullptr;  // the bias does not reach dx
     wtconv_desc f = d;
     f.L = 1;
+    const PhaseExec pe = choose_phase(f, dx1 != nullptr);
+    if (pe.kind != PhaseExec::None) return phase_pass(f, pe, dy, pr, dx, skip_base, dx1, stream, nullptr);
     const Exec fx = choose(f, false);
     if (fx.mode != Mode::Region && fx.mode != Mode::Resident) return WTCONV_ERR_UNSUPPORTED;
     const FusedPass fp = fused_pass(f, fx);
@@ -1471,7 +1787,9 @@ wtconv_status partials_impl(const wtconv_desc& d, const void* x, const void* dy,
         pr.rot = 1;
         pr.b0 = nullptr;  // the bias does not reach dx
         Plan dxp;
-        const bool dx_carry = dx && ge.coarse && dx_pass_plan(d, ge.Lf, dxp);
+        // (A polyphase forward takes every level of the plane in its one launch
+        // and needs no such carry.)
+        const bool dx_carry = dx && ge.coarse && choose_phase(d).kind != PhaseExec::Resident && dx_pass_plan(d, ge.Lf, dxp);
         wtconv_status st = WTCONV_OK;
         void* dx1 = nullptr;
         if (ge.coarse) {

@@ -1,0 +1,70 @@
+"""Polyphase kernels on the matrix cores: parity with the float64 oracle at the
+sizes where their tiling can go wrong, and non-finite inputs.
+
+Shapes: widths around the 8-column tiles and the 4-column blocks (odd ones
+read rows at any alignment), heights around the two-row pairs and the vertical
+segments, planes of 1 to 5 stages whose grids end at 1 x 1, batches that do not
+fill the last group of resident planes, planes in region tiles whose last tile
+is partial. The tolerances are the operator's (1e-5 of the largest value in
+float32, 2e-2 in 16 bits)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2608_10805_amd import binding
+from tests._gpu import TOL, rel_err, setup, to_np
+
+pytestmark = pytest.mark.gpu
+
+FORWARD = [
+    (1, 1, 9, 4, 5, 1, "f32"), (3, 2, 9, 9, 3, 1, "f32"), (5, 2, 16, 17, 5, 2, "f32"), (7, 3, 15, 8, 5, 2, "bf16"),
+    (2, 2, 31, 33, 5, 3, "f16"), (3, 1, 57, 55, 5, 3, "f32"), (2, 2, 56, 56, 5, 5, "bf16"), (19, 2, 14, 14, 5, 3, "bf16"),
+    (4, 2, 63, 95, 5, 3, "f32"), (2, 1, 65, 94, 3, 4, "bf16"), (6, 2, 12, 100, 3, 2, "f16"), (2, 2, 100, 10, 5, 2, "bf16"),
+    (11, 3, 20, 20, 3, 5, "f16"), (2, 2, 28, 30, 5, 4, "bf16"), (2, 1, 129, 131, 5, 1, "f32"), (2, 2, 120, 160, 5, 3, "bf16"),
+    (1, 2, 226, 225, 3, 2, "f32"), (2, 1, 97, 203, 5, 2, "f16"),
+]
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", FORWARD)
+def test_forward_and_dx(B, C, H, W, k, L, dtype):
+    inp, dev = setup(B, C, H, W, k, L, dtype, seed=B + H + W)
+    want = oracle.forward(inp.x, inp.base_w, inp.base_scale, inp.level_w, inp.level_scale)
+    assert rel_err(to_np(dev.forward()), want) < TOL[dtype]
+    dx = binding.backward_data(dev.dy, dev.bw, dev.bs, dev.lw, dev.ls)
+    torch.cuda.synchronize()
+    ref = oracle.backward(inp.x, inp.dy, inp.base_w, inp.base_scale, inp.level_w, inp.level_scale)
+    assert rel_err(to_np(dx), ref["dx"]) < TOL[dtype]
+
+
+def footprint(H, W, y, x, k, L):
+    """Outputs that depend on pixel (y, x): those whose 2^L x 2^L block lies
+    within k // 2 blocks of the pixel's (the coarsest level's window holds
+    every finer one's, and the base kernel's)."""
+    R, m = k // 2, np.zeros((H, W), bool)
+    j, i = y >> L, x >> L
+    m[max(0, (j - R) << L):(j + R + 1) << L, max(0, (i - R) << L):(i + R + 1) << L] = True
+    return m
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", [(3, 2, 56, 56, 5, 1, "f32"), (2, 2, 40, 41, 5, 2, "bf16"),
+                                               (5, 2, 28, 28, 3, 3, "f16"), (2, 1, 130, 128, 5, 1, "bf16")])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_non_finite_pixels_reach_their_outputs_only(B, C, H, W, k, L, dtype, value):
+    """A non-finite pixel makes exactly the outputs that depend on it
+    non-finite; every other value is the one without it."""
+    _, dev = setup(B, C, H, W, k, L, dtype, seed=7)
+    spots = [(0, 0, H // 3, W // 2 + 1), (B - 1, C - 1, H - 1, 0)]
+    clean = dev.x.clone()
+    for b, c, y, x in spots:
+        clean[b, c, y, x] = 0
+    want = binding.forward(clean, dev.bw, dev.bs, dev.lw, dev.ls)
+    for b, c, y, x in spots:
+        dev.x[b, c, y, x] = value
+    got = dev.forward()
+    bad = np.zeros((B, C, H, W), bool)
+    for b, c, y, x in spots:
+        bad[b, c] |= footprint(H, W, y, x, k, L)
+    assert np.array_equal(~torch.isfinite(got).cpu().numpy(), bad)
+    keep = torch.from_numpy(~bad).to(got.device)
+    assert torch.equal(got[keep], want[keep])
