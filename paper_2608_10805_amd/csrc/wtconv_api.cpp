@@ -954,8 +954,17 @@ bool make_grad_plan(const wtconv_desc& d, GradPlan& gp)
     return true;
 }
 
+// The gradient pass on the matrix cores (wtconv_phase_grad.hip).
+struct PhaseGradPlan {
+    wtc::PhaseGradArgs a;  // geometry, LDS layout, nb and PP (pointers unset)
+    int rounds = 1;        // 4 x 4 block rounds per thread and side
+    int nchunks = 1;
+};
+
 struct GradExec {
     bool use = false;
+    bool phase = false;  // polyphase kernel `pg` (then Lf = L, and gp holds nchunks alone)
+    PhaseGradPlan pg;
     GradPlan gp;
     int Lf = 0;           // levels whose kernel gradients grad_kernel forms
     bool coarse = false;  // levels Lf+1..L: backward of the coarse sub-problem on X_m, dY_m
@@ -1007,6 +1016,174 @@ bool grad_pass_pays_deep(const wtconv_desc& d)
     return d.k >= 5;
 }
 
+// ----------------------------------------------------------------------------
+// Polyphase gradient pass
+// ----------------------------------------------------------------------------
+bool phase_grad_layout(const wtconv_desc& d, wtc::PhaseGradArgs& a)
+{
+    constexpr int M = wtc::kPhaseMargin;
+    const int R = d.k / 2;
+    long off = 0;
+    a.sx.margin = M;
+    a.sd.margin = 0;
+    for (int s = 0; s < a.L; ++s) {
+        const int np = s == 0 ? 1 : 3;          // pieces
+        const int rows = 2 * a.V[s] * a.js[s];  // rows the runs cover
+        const int bx = a.dbx, by = a.dby;       // blocks of the counted area
+        const int cover = s == 0 ? 4 * by : (s == 1 ? 2 * by : (s == 2 ? by : a.h[s]));
+        const int wide = s == 0 ? 4 * bx : (s == 1 ? 2 * bx : (s == 2 ? bx : a.w[s]));
+        const int xcover = cover + (a.rg_ntx > 0 ? M : 0);
+        a.sx.pitch[s] = 8 * ((a.ct[s] + 1) | 1);
+        a.sx.psz[s] = ceil_to((M + std::max(xcover, rows + 2 * R)) * a.sx.pitch[s] * 2, 16);
+        a.sx.off[s] = (int)off;
+        off += (long)np * a.sx.psz[s];
+        a.sd.pitch[s] = 8 * (std::max(a.ct[s], cdiv(wide, 8)) | 1);
+        a.sd.psz[s] = ceil_to(std::max(cover, rows) * a.sd.pitch[s] * 2, 16);
+        a.sd.off[s] = (int)off;
+        off += (long)np * a.sd.psz[s];
+        if (s >= 2 && s + 1 < a.L)
+            for (wtc::PhaseSide* g : {&a.sx, &a.sd}) {
+                g->mf[s] = (int)off;
+                off += ceil_to(a.h[s] * a.w[s] * 4, 16);
+            }
+        a.r_ct[s] = 1.0f / (float)a.ct[s];
+        a.r_vct[s] = 1.0f / (float)(a.V[s] * a.ct[s]);
+        if (off > (1L << 24)) return false;
+    }
+    a.plane_bytes = (int)off;
+    // the planes, then (after the last batch) one stage's matrix gradient
+    const long total = std::max<long>(a.PP * off, 2 * d.k * 256 * 4);
+    if (total > 160 * 1024) return false;
+    a.lds_bytes = (int)total;
+    a.r_xbx = 1.0f / (float)a.xbx;
+    a.r_xb = 1.0f / (float)(a.xbx * a.xby);
+    a.r_dbx = 1.0f / (float)a.dbx;
+    a.r_db = 1.0f / (float)(a.dbx * a.dby);
+    return true;
+}
+
+int phase_grad_wgs(const PhaseGradPlan& pg)
+{
+    const int regs = pg.a.L > 3 || pg.rounds == 2 ? 2 : 3;
+    return std::max(1, std::min(regs, lds_wgs(cdiv(pg.a.lds_bytes, 4))));
+}
+
+// Modeled cycles of one batch of a workgroup, as phase_cycles().
+double phase_grad_cycles(const wtconv_desc& d, const PhaseGradPlan& pg)
+{
+    const wtc::PhaseGradArgs& a = pg.a;
+    const double fine = cdiv(a.PP * a.V[0] * a.ct[0], 32 * a.fine_waves) *
+                        (32.0 * a.js[0] * d.k + 60.0 * (a.js[0] + d.k));
+    double deep = 0, last = 0;  // one wavefront per deeper stage, stages 3 and 4 share one
+    for (int s = 1; s < a.L; ++s) {
+        const double c = cdiv(a.PP * a.V[s] * a.ct[s], 32) * (32.0 * d.k * 6 + 80.0 * (1 + d.k));
+        if (s < 3)
+            deep = std::max(deep, c);
+        else
+            last += c + 600;
+    }
+    return std::max(fine, std::max(deep, last)) + (d.L > 1 ? 1200 : 500) * pg.rounds + 500;
+}
+
+void phase_grad_grid(int s, int h, int w, int js, wtc::PhaseGradArgs& a)
+{
+    a.h[s] = h;
+    a.w[s] = w;
+    a.ct[s] = cdiv(w, 8);
+    a.js[s] = js;
+    a.V[s] = cdiv((h + 1) / 2, js);
+}
+
+constexpr int kPhaseGradJs0 = 4;  // row pairs per run of stage 0 (the kernel's)
+
+bool make_phase_grad_plan(const wtconv_desc& d, PhaseGradPlan& out)
+{
+    double best = -1;
+    const long HW = (long)d.H * d.W;
+    for (int PP = 1; PP <= std::min(d.B, 32); ++PP) {
+        if (((PP - 1L) * d.C + 1) * HW >= 1L << 29) break;  // 32-bit byte offsets within a batch
+        PhaseGradPlan pg;
+        wtc::PhaseGradArgs& a = pg.a;
+        memset(&a, 0, sizeof(a));
+        a.B = d.B;
+        a.C = d.C;
+        a.H = d.H;
+        a.W = d.W;
+        a.L = d.L;
+        a.PP = PP;
+        a.fine_waves = std::max(1, 5 - d.L);
+        a.xbx = a.dbx = ceil_to(d.W, 4) / 4;
+        a.xby = a.dby = ceil_to(d.H, 4) / 4;
+        const long blocks = (long)PP * a.xbx * a.xby;
+        if (blocks > 2 * wtc::kThreads) break;
+        pg.rounds = blocks > wtc::kThreads ? 2 : 1;
+        int h = d.H, w = d.W;
+        for (int s = 0; s < d.L; ++s) {
+            phase_grad_grid(s, h, w, s == 0 ? kPhaseGradJs0 : 1, a);
+            h = (h + 1) / 2;
+            w = (w + 1) / 2;
+        }
+        if (!phase_grad_layout(d, a)) continue;
+        const int slots = 256 * phase_grad_wgs(pg);
+        const int chunks = std::max(1, std::min(cdiv(d.B, PP), slots / std::max(1, d.C)));
+        a.nb = ceil_to(cdiv(d.B, chunks), PP);
+        pg.nchunks = cdiv(d.B, a.nb);
+        const long grid = (long)pg.nchunks * d.C;
+        const double score = (phase_grad_cycles(d, pg) * (a.nb / PP) + 3000) * ((grid + slots - 1) / slots);
+        if (best < 0 || score < best) {
+            best = score;
+            out = pg;
+        }
+    }
+    return best >= 0;
+}
+
+// Region tiles of the gradient route (edge T, batch chunks of nb planes).
+bool make_phase_grad_region(const wtconv_desc& d, int T, int ntx, int nty, int nb, PhaseGradPlan& pg)
+{
+    if (T % 8 != 0 || T > 56) return false;  // one block round of the tile with its halo
+    wtc::PhaseGradArgs& a = pg.a;
+    memset(&a, 0, sizeof(a));
+    a.B = d.B;
+    a.C = d.C;
+    a.H = d.H;
+    a.W = d.W;
+    a.L = 1;
+    a.PP = 1;
+    a.nb = nb;
+    a.fine_waves = 4;
+    a.rg_ntx = ntx;
+    a.rg_nty = nty;
+    a.rg_T = T;
+    a.dbx = a.dby = T / 4;
+    a.xbx = a.xby = T / 4 + 2;
+    phase_grad_grid(0, T, T, kPhaseGradJs0, a);
+    pg.rounds = 1;
+    return phase_grad_layout(d, a);
+}
+
+bool phase_grad_offered(const wtconv_desc& d)
+{
+    // 16-bit storage: one exact product per term. (float32 needs six, took as
+    // long as the vector kernels, 56 x 56 B64 C96 L3 training step 230 against
+    // 205 us, and its longer chains lost a factor of two in the error.)
+    return wtc::launch_phase_grad && d.dtype != WTCONV_F32 && (d.k == 3 || d.k == 5) && d.L >= 1 && d.L <= wtc::kPhaseMaxStages && d.W >= 4 &&
+           !use_tiny(d);
+}
+
+// Where the polyphase gradient pass is the faster one. Measured on MI355X,
+// training step with it / with the vector gradient pass (bf16, k = 5 and 3):
+// 0.45 (63 x 95 L1) to 0.95, most 0.6-0.85; 14 x 14 L5 B128 C384, where the
+// one-plane-per-lane coarse kernel has enough planes, 1.13; 56 x 56 L4 and L5
+// with 1536 planes (four deeper stages hold it to two workgroups per CU) 1.05.
+bool phase_grad_pays(const wtconv_desc& d)
+{
+    const int edge = std::max(d.H, d.W);
+    const long planes = (long)d.B * d.C;
+    if (d.L == 5 && edge <= 16 && planes >= kSplitMinPlanes) return false;
+    return d.L <= 3 || edge <= 48 || planes >= 4096;
+}
+
 GradExec choose_grad_uncached(const wtconv_desc& d);
 
 GradExec choose_grad(const wtconv_desc& d)
@@ -1019,6 +1196,12 @@ GradExec choose_grad_uncached(const wtconv_desc& d)
 {
     GradExec ge;
     if (use_tiny(d) || d.L < 1) return ge;
+    if (phase_grad_offered(d) && phase_grad_pays(d) && make_phase_grad_plan(d, ge.pg)) {
+        ge.use = ge.phase = true;
+        ge.gp.nchunks = ge.pg.nchunks;
+        ge.Lf = d.L;
+        return ge;
+    }
     const int m = tiny_level(d);
     if (m < 1 || (m == 1 && d.L > 2 && !grad_pass_pays_deep(d))) return ge;
     wtconv_desc f = d;
@@ -1651,6 +1834,22 @@ wtconv_status grad_pass(const wtconv_desc& d, const GradExec& ge, const void* x,
                         int skip_base, hipStream_t stream, void* cx = nullptr, void* cdy = nullptr, int cm = 0,
                         const RegionPlan* rp = nullptr)
 {
+    if (ge.phase) {
+        wtc::PhaseGradArgs a = ge.pg.a;
+        a.x = x;
+        a.dy = dy;
+        a.partial = partial;
+        a.skip_base = skip_base;
+        if (cx) {
+            const wtconv_desc cd = coarse_desc(d, 1);
+            a.cx = cx;
+            a.cdy = cdy;
+            a.cH = cd.H;
+            a.cW = cd.W;
+        }
+        const int grid = (rp ? rp->pl.nchunks * rp->ntx * rp->nty : ge.pg.nchunks) * d.C;
+        return hip_status(wtc::launch_phase_grad(d.k, d.dtype, a, grid, ge.pg.rounds, stream));
+    }
     wtc::GradArgs a;
     memset(&a, 0, sizeof(a));
     int grid = ge.gp.nchunks * d.C;
@@ -1717,6 +1916,9 @@ bool region_grad_exec(const wtconv_desc& d, const Exec& ex, GradExec& ge)
     ge.use = true;
     ge.Lf = 1;
     ge.coarse = ex.coarse;
+    rd = d;
+    rd.L = 1;
+    ge.phase = phase_grad_offered(rd) && make_phase_grad_region(d, ex.rp.T, ex.rp.ntx, ex.rp.nty, ex.rp.pl.nb, ge.pg);
     return true;
 }
 

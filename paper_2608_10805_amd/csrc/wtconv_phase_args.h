@@ -72,9 +72,50 @@ struct PhaseArgs {
     PhaseStage st[kPhaseMaxStages];
 };
 
+// Kernel gradients in the polyphase formulation (wtconv_phase_grad.hip): the
+// gradient of stage s's 16 x 16 k weight matrix is the product of its output
+// gradients' tiles (the block means D_s of dy) with the windows of X_s.
+// One operand side (x or dy) of every stage in LDS, per plane:
+struct PhaseSide {
+    int margin;  // zero rows and columns before the first pixel
+    int off[kPhaseMaxStages];    // byte offset of piece 0 in the plane's region
+    int pitch[kPhaseMaxStages];  // 16-bit elements per row (multiple of 8)
+    int psz[kPhaseMaxStages];    // bytes per piece
+    int mf[kPhaseMaxStages];     // s >= 2, when a deeper stage reads it: the means in float32 (w floats per row)
+};
+
+struct PhaseGradArgs {
+    const void* x;
+    const void* dy;
+    float* partial;  // [nchunks (* tiles)][C][NP] kernel-gradient partials
+    int B, C, H, W;
+    int nb, PP, L;
+    int skip_base;
+    int fine_waves;   // wavefronts on stage 0: 4 (L = 1), 3 (L = 2), 2 (L = 3) or 1; then one per deeper stage
+                      // (the fourth takes stages 3 and 4)
+    int plane_bytes, lds_bytes;
+    int xbx, xby;     // 4 x 4 blocks of x per row / column of the loaded area
+    int dbx, dby;     // of dy
+    float r_xbx, r_xb, r_dbx, r_db;  // 1 / xbx, 1 / (xbx xby), 1 / dbx, 1 / (dbx dby)
+    int h[kPhaseMaxStages], w[kPhaseMaxStages];   // grids
+    int ct[kPhaseMaxStages];                      // 8-column tiles per row
+    int V[kPhaseMaxStages], js[kPhaseMaxStages];  // vertical segments, row pairs each
+    float r_ct[kPhaseMaxStages], r_vct[kPhaseMaxStages];
+    PhaseSide sx, sd;
+    // Region mode (rg_ntx > 0, L = 1): rg_T x rg_T tiles; x is loaded with one
+    // block of halo, dy without. cx, cdy (nullable): the level-1 carriers of x
+    // and dy of the tile's own pixels, [B][C][cH][cW].
+    int rg_ntx, rg_nty, rg_T;
+    void* cx;
+    void* cdy;
+    int cH, cW;
+};
+
 // Weak: the planner's host tests link without the kernels; the phase route is
 // then not offered.
 hipError_t launch_phase_forward(int k, wtconv_dtype dt, const PhaseArgs& a, int grid, int block_rounds,
                                 hipStream_t s) __attribute__((weak));
+hipError_t launch_phase_grad(int k, wtconv_dtype dt, const PhaseGradArgs& a, int grid, int block_rounds,
+                             hipStream_t s) __attribute__((weak));
 
 }  // namespace wtc

@@ -68,3 +68,39 @@ def test_non_finite_pixels_reach_their_outputs_only(B, C, H, W, k, L, dtype, val
     assert np.array_equal(~torch.isfinite(got).cpu().numpy(), bad)
     keep = torch.from_numpy(~bad).to(got.device)
     assert torch.equal(got[keep], want[keep])
+
+
+GRADIENT = [
+    (1, 1, 9, 4, 5, 1, "bf16"), (3, 2, 11, 9, 3, 1, "f16"), (5, 2, 16, 17, 5, 2, "bf16"), (34, 1, 14, 14, 5, 2, "bf16"),
+    (2, 2, 31, 33, 5, 3, "f16"), (3, 1, 57, 55, 5, 3, "bf16"), (3, 2, 48, 48, 5, 5, "bf16"), (19, 2, 14, 14, 3, 3, "bf16"),
+    (4, 2, 63, 95, 5, 3, "bf16"), (2, 1, 65, 94, 3, 4, "bf16"), (6, 2, 12, 100, 3, 2, "f16"), (2, 2, 100, 10, 5, 2, "bf16"),
+    (11, 3, 20, 20, 3, 5, "f16"), (2, 2, 28, 30, 5, 4, "bf16"), (7, 2, 40, 10, 5, 3, "f16"), (2, 1, 129, 131, 5, 1, "bf16"),
+    (1, 2, 226, 225, 3, 1, "f16"),
+]
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", GRADIENT)
+def test_kernel_gradients(B, C, H, W, k, L, dtype):
+    """16-bit inputs, float32 sums: every kernel gradient (and the bias's) to
+    float32 accuracy on planes whose levels run in one pass or have one level
+    (no intermediate is rounded to the storage type)."""
+    inp, dev = setup(B, C, H, W, k, L, dtype, seed=B + 3 * H + W)
+    bias = torch.linspace(-0.5, 0.5, C, device=dev.x.device)
+    out = binding.backward(dev.x, dev.dy, dev.bw, dev.bs, dev.lw, dev.ls, bias=bias, need_dbias=True)
+    torch.cuda.synchronize()
+    ref = oracle.backward(inp.x, inp.dy, inp.base_w, inp.base_scale, inp.level_w, inp.level_scale)
+    assert rel_err(to_np(out[0]), ref["dx"]) < TOL[dtype]
+    assert rel_err(to_np(out[1]), ref["d_base_w"]) < 1e-5
+    sdy = np.asarray(inp.dy, np.float64).sum((0, 2, 3))
+    assert rel_err(to_np(out[2]), ref["d_base_scale"] + to_np(bias) * sdy) < 1e-5
+    assert rel_err(to_np(out[5]), np.asarray(inp.base_scale, np.float64) * sdy) < 1e-5
+    for l in range(L):
+        assert rel_err(to_np(out[3][l]), ref["d_level_w"][l]) < 1e-5
+        assert rel_err(to_np(out[4][l]), ref["d_level_scale"][l]) < 1e-5
+
+
+def test_kernel_gradients_bitwise_reproducible():
+    _, dev = setup(5, 3, 33, 35, 5, 4, "bf16", seed=3)
+    a, b = dev.backward(), dev.backward()
+    for p, q in zip((a[1], a[2], *a[3], *a[4]), (b[1], b[2], *b[3], *b[4])):
+        assert torch.equal(p, q)
