@@ -1168,7 +1168,7 @@ bool phase_grad_offered(const wtconv_desc& d)
     // long as the vector kernels, 56 x 56 B64 C96 L3 training step 230 against
     // 205 us, and its longer chains lost a factor of two in the error.)
     return wtc::launch_phase_grad && d.dtype != WTCONV_F32 && (d.k == 3 || d.k == 5) && d.L >= 1 && d.L <= wtc::kPhaseMaxStages && d.W >= 4 &&
-           !use_tiny(d);
+           (!use_tiny(d) || d.L == 1);  // tiny planes: L = 1 alone (training step 7 x 7 B128 C768 71 -> 58 us, L2 79 -> 96)
 }
 
 // Where the polyphase gradient pass is the faster one. Measured on MI355X,
@@ -1195,13 +1195,14 @@ GradExec choose_grad(const wtconv_desc& d)
 GradExec choose_grad_uncached(const wtconv_desc& d)
 {
     GradExec ge;
-    if (use_tiny(d) || d.L < 1) return ge;
+    if (d.L < 1) return ge;
     if (phase_grad_offered(d) && phase_grad_pays(d) && make_phase_grad_plan(d, ge.pg)) {
         ge.use = ge.phase = true;
         ge.gp.nchunks = ge.pg.nchunks;
         ge.Lf = d.L;
         return ge;
     }
+    if (use_tiny(d)) return ge;
     const int m = tiny_level(d);
     if (m < 1 || (m == 1 && d.L > 2 && !grad_pass_pays_deep(d))) return ge;
     wtconv_desc f = d;
@@ -1515,7 +1516,14 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
 PhaseExec choose_phase(const wtconv_desc& d, bool region = false)
 {
     PhaseExec none;
-    if (!wtc::launch_phase_forward || (d.k != 3 && d.k != 5) || d.L < 1 || d.W < 4 || use_tiny(d)) return none;
+    if (!wtc::launch_phase_forward || (d.k != 3 && d.k != 5) || d.L < 1 || d.W < 4) return none;
+    // Planes of at most 8 x 8 have the one-plane-per-lane kernel. At L = 1 in 16
+    // bits the polyphase one is faster on rows of whole vectors (8 x 8 B128 C768
+    // 18.5 -> 13.7 us) and where 64 planes per wavefront leave the chip idle
+    // (7 x 7 B32 C256 12.9 -> 8.7; B128 C768 18.9 -> 19.8 stays).
+    if (use_tiny(d) &&
+        (d.dtype == WTCONV_F32 || d.L > 1 || (d.W % 4 != 0 && (long)d.B * d.C >= kSplitMinPlanes)))
+        return none;
     static PlanCache<PhaseExec> cache;
     return cache.get(d, region ? 1 : 0, [&] {
         PhaseExec e;

@@ -22,7 +22,8 @@ FORWARD = [
     (2, 2, 31, 33, 5, 3, "f16"), (3, 1, 57, 55, 5, 3, "f32"), (2, 2, 56, 56, 5, 5, "bf16"), (19, 2, 14, 14, 5, 3, "bf16"),
     (4, 2, 63, 95, 5, 3, "f32"), (2, 1, 65, 94, 3, 4, "bf16"), (6, 2, 12, 100, 3, 2, "f16"), (2, 2, 100, 10, 5, 2, "bf16"),
     (11, 3, 20, 20, 3, 5, "f16"), (2, 2, 28, 30, 5, 4, "bf16"), (2, 1, 129, 131, 5, 1, "f32"), (2, 2, 120, 160, 5, 3, "bf16"),
-    (1, 2, 226, 225, 3, 2, "f32"), (2, 1, 97, 203, 5, 2, "f16"),
+    (1, 2, 226, 225, 3, 2, "f32"), (2, 1, 97, 203, 5, 2, "f16"), (3, 2, 7, 7, 5, 1, "bf16"), (70, 1, 8, 8, 3, 1, "f16"),
+    (9, 3, 5, 4, 5, 1, "bf16"), (65, 130, 8, 4, 5, 1, "bf16"),
 ]
 
 
@@ -75,7 +76,8 @@ GRADIENT = [
     (2, 2, 31, 33, 5, 3, "f16"), (3, 1, 57, 55, 5, 3, "bf16"), (3, 2, 48, 48, 5, 5, "bf16"), (19, 2, 14, 14, 3, 3, "bf16"),
     (4, 2, 63, 95, 5, 3, "bf16"), (2, 1, 65, 94, 3, 4, "bf16"), (6, 2, 12, 100, 3, 2, "f16"), (2, 2, 100, 10, 5, 2, "bf16"),
     (11, 3, 20, 20, 3, 5, "f16"), (2, 2, 28, 30, 5, 4, "bf16"), (7, 2, 40, 10, 5, 3, "f16"), (2, 1, 129, 131, 5, 1, "bf16"),
-    (1, 2, 226, 225, 3, 1, "f16"),
+    (1, 2, 226, 225, 3, 1, "f16"), (3, 2, 7, 7, 5, 1, "bf16"), (70, 1, 8, 8, 3, 1, "f16"), (9, 3, 5, 4, 5, 1, "bf16"),
+    (65, 3, 8, 5, 3, 1, "bf16"),
 ]
 
 
