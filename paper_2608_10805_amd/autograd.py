@@ -3,6 +3,7 @@
 Only x and the parameters are saved for backward (no per-level subband
 tensors): the backward kernel recomputes both Haar pyramids on chip.
 """
+import ctypes
 import math
 
 import torch
@@ -36,7 +37,39 @@ class WTConvFunction(torch.autograd.Function):
         return (dx, dbw, dbs, dbb, *dlw, *dls)
 
 
+_native = None
+
+
+def _load_native():
+    """The native host path (csrc/wtconv_torch.cpp), given the library's entry
+    points; False where it was not built."""
+    global _native
+    if _native is None:
+        try:
+            from . import _wtconv_torch as ext
+        except ImportError:
+            _native = False
+        else:
+            lib = binding.load()
+            ext.init(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value
+                       for n in ("wtconv_forward_workspace_bytes", "wtconv_forward",
+                                 "wtconv_backward_workspace_bytes", "wtconv_backward", "wtconv_status_string")))
+            _native = ext
+    return _native
+
+
 def wtconv(x, base_w, base_scale, level_w, level_scale, base_bias=None):
+    """The operator under autograd. The plain case (dense, contiguous GPU tensors
+    that fit the problem, nothing tracing or transforming) runs from native
+    code; WTConvFunction does the same for every other one, or raises."""
+    ext = _native if _native is not None else _load_native()
+    if ext and len(level_w) == len(level_scale) and not torch.compiler.is_compiling():
+        try:
+            y = ext.apply(x, base_w, base_scale, base_bias, [*level_w, *level_scale])
+        except TypeError:  # an argument that is no tensor
+            y = None
+        if y is not None:
+            return y
     return WTConvFunction.apply(x, base_w, base_scale, base_bias, *level_w, *level_scale)
 
 

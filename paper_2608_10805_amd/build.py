@@ -21,6 +21,9 @@ SOURCES = ["wtconv_api.cpp", "wtconv_noalloc.cpp", "wtconv_fwd.hip", "wtconv_mix
 # measurement helper used only by the benchmark (sustained VALU rate)
 PROBE_LIB = os.path.join(HERE, "libvalu_probe.so")
 PROBE_SOURCES = ["valu_probe.hip"]
+# native host path of the autograd wrapper: a Python extension against torch's headers
+TORCH_LIB = os.path.join(HERE, "_wtconv_torch.so")
+TORCH_SOURCE = "wtconv_torch.cpp"
 ARCH = os.environ.get("WTCONV_OFFLOAD_ARCH", "gfx950")
 
 
@@ -55,10 +58,31 @@ def _compile(sources, lib, extra, verbose):
     os.replace(lib + ".tmp", lib)
 
 
+def _compile_torch(verbose):
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    includes = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
+                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-DTORCH_EXTENSION_NAME=_wtconv_torch",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE]
+    for d in includes:
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, TORCH_SOURCE), "-o", TORCH_LIB + ".tmp", "-L", os.path.join(t, "lib"), "-lc10",
+            "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(TORCH_LIB + ".tmp", TORCH_LIB)
+
+
 def build(verbose: bool = False, extra=None) -> str:
-    """Compile every HIP source (libwtconv.so and the benchmark's VALU probe)
-    and return the path of libwtconv.so."""
+    """Compile every HIP source (libwtconv.so and the benchmark's VALU probe) and
+    the autograd wrapper's native host path; return the path of libwtconv.so."""
     _compile(SOURCES, LIB, extra, verbose)
+    _compile_torch(verbose)
     _compile(PROBE_SOURCES, PROBE_LIB, extra, verbose)
     return LIB
 
