@@ -1366,7 +1366,7 @@ double phase_chunks(const wtconv_desc& d, PhasePlan& pp, int tiles)
     // one round of resident workgroups where the batch allows it
     const int slots = 256 * phase_wgs(d, pp.a, pp.rounds);
     const int chunks = std::max(1, std::min(cdiv(d.B, pp.a.PP), slots / std::max(1, d.C * tiles)));
-    pp.a.nb = std::min(ceil_to(cdiv(d.B, chunks), pp.a.PP), 32768 * pp.a.PP);  // batches are numbered in 16 bits
+    pp.a.nb = std::min(ceil_to(cdiv(d.B, chunks), pp.a.PP), 32000 * pp.a.PP);  // batches are numbered in 15 bits
     pp.nchunks = cdiv(d.B, pp.a.nb);
     const long grid = (long)pp.nchunks * d.C * tiles;
     return phase_cycles(d, pp.a, pp.rounds) * (pp.a.nb / pp.a.PP) * ((grid + slots - 1) / slots);

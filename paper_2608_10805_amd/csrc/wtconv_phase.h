@@ -4,9 +4,8 @@
 //
 // Operands. The matrix cores take 16-bit operands and accumulate in float32.
 // A float32 value is split exactly into three bfloat16 pieces h + m + l (8
-// bits each, round to nearest), and a product keeps the six piece products
-// down to 2^-16 of it; the dropped ones are below 2^-26, under the rounding of
-// one float32 FMA. bfloat16 and float16 storage needs one piece for the
+// bits each), and a product keeps the six piece products down to 2^-16 of it;
+// the dropped ones are below 2^-24 together, about one float32 rounding. bfloat16 and float16 storage needs one piece for the
 // input itself (bfloat16 / float16 matrix instructions) and three / two for
 // the float32 weights; the block means of deeper stages are split in three.
 #pragma once
@@ -63,14 +62,23 @@ DEV uint32_t pk_f16(float a, float b)
 DEV float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 DEV float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
-// Two finite floats -> packed bfloat16 pieces h, m, l with v = h + m + l (exact
-// up to 2^-26 of v).
+// Two finite floats -> packed bfloat16 pieces h, m, l with v = h + m + l exactly.
+// h is cut off, not rounded: next to the largest float (a mask's lowest value)
+// rounding would make it infinite, and 0 * inf would reach outputs that do not
+// depend on the pixel.
 DEV void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
 {
-    h = pk_bf16(a, b);
-    const float ra = a - bf_lo(h), rb = b - bf_hi(h);
+    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+    const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
     m = pk_bf16(ra, rb);
     l = pk_bf16(ra - bf_lo(m), rb - bf_hi(m));
+}
+
+// Mean of four values, finite for finite ones (their sum need not be).
+DEV float mean4(float a, float b, float c, float d)
+{
+    return __builtin_fmaf(0.25f, d, __builtin_fmaf(0.25f, c, __builtin_fmaf(0.25f, b, 0.25f * a)));
 }
 
 template <bool F16>

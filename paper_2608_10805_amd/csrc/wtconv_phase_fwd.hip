@@ -68,7 +68,7 @@ DEV void coarse_stage_js(const PhaseArgs& a, char* lds, int s, bool carry, int l
             }
         }
         run_tiles<K, JS, DeepScheme, JS, WHOLE>(lds, bp, 4 * g.pitch, g.psz, A, acc);
-const int x = 8 * I + 4 * (grp & 1);
+        const int x = 8 * I + 4 * (grp & 1);
 #pragma unroll
         for (int J = 0; J < JS; ++J)
             if (live)
@@ -125,7 +125,7 @@ DEV void build_deep(const PhaseArgs& a, char* lds, int s, int lane)
         const bool bx = 2 * i + 1 < gp.w, by = 2 * j + 1 < gp.h;
         const float v00 = src[0], v01 = bx ? src[1] : 0.f;
         const float v10 = by ? src[gp.w] : 0.f, v11 = (bx && by) ? src[gp.w + 1] : 0.f;
-        const float v = 0.25f * ((v00 + v01) + (v10 + v11));
+        const float v = mean4(v00, v01, v10, v11);
         if (s + 1 < a.L) reinterpret_cast<float*>(plane + g.mf)[j * g.w + i] = v;
         uint32_t h, m, l;
         split2(v, 0.f, h, m, l);
@@ -180,7 +180,7 @@ DEV void put_block(const PhaseArgs& a, char* plane, int y0, int x0, const RawBlo
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            s1[i][j] = 0.25f * ((v[2 * i][2 * j] + v[2 * i][2 * j + 1]) + (v[2 * i + 1][2 * j] + v[2 * i + 1][2 * j + 1]));
+            s1[i][j] = mean4(v[2 * i][2 * j], v[2 * i][2 * j + 1], v[2 * i + 1][2 * j], v[2 * i + 1][2 * j + 1]);
         uint32_t h, m, l;
         split2(s1[i][0], s1[i][1], h, m, l);
         char* q = plane + g1.poff + 2 * (((y0 >> 1) + i + M) * g1.pitch + (x0 >> 1) + M);
@@ -190,7 +190,7 @@ DEV void put_block(const PhaseArgs& a, char* plane, int y0, int x0, const RawBlo
     }
     if (a.L < 3) return;
     const PhaseStage& g2 = a.st[2];
-    const float s2 = 0.25f * ((s1[0][0] + s1[0][1]) + (s1[1][0] + s1[1][1]));
+    const float s2 = mean4(s1[0][0], s1[0][1], s1[1][0], s1[1][1]);
     uint32_t h, m, l;
     split2(s2, 0.f, h, m, l);
     uint16_t* q = reinterpret_cast<uint16_t*>(plane + g2.poff) + ((y0 >> 2) + M) * g2.pitch + (x0 >> 2) + M;
@@ -222,7 +222,15 @@ DEV void store4(ST* __restrict__ base, uint32_t off, int x, int xe, const float 
 
 // Marks of non-finite input pixels (LDS, 16-bit): one per resident plane, then
 // one per cell of its loaded blocks (2 x 2 pixels for L = 1, else 4 x 4). A
-// mark holds the number of the batch that set it, so nothing is cleared.
+// mark holds twice the number of the last batch that set it, so nothing is
+// cleared, plus one if the batch before set it too: a wavefront may mark batch
+// n + 1 while another still stores batch n (never n - 1: two barriers apart).
+DEV void set_mark(uint16_t& m, uint16_t epoch)
+{
+    const int last = m >> 1;
+    if (last != epoch) m = (uint16_t)(2 * epoch + (last + 1 == epoch));
+}
+DEV bool marked(uint16_t m, uint16_t epoch) { return (m >> 1) == epoch || m == 2 * (epoch + 1) + 1; }
 DEV int mark_cells(const PhaseArgs& a) { return a.L == 1 ? 4 * a.bx * a.by : a.bx * a.by; }
 
 // Zeroes the non-finite pixels of block e of plane p and marks their cells.
@@ -231,13 +239,14 @@ DEV void mark_block(const PhaseArgs& a, char* lds, int p, int e, uint16_t epoch,
 {
     uint16_t* marks = reinterpret_cast<uint16_t*>(lds + a.mark_off);
     uint16_t* cell = marks + a.PP + p * mark_cells(a);
-    marks[p] = epoch;
+    set_mark(marks[p], epoch);
     const int j = fdiv(e, a.r_bx), i = e - j * a.bx;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            if (drop_nonfinite<ST>(v, r, h)) cell[a.L == 1 ? (2 * j + (r >> 1)) * 2 * a.bx + 2 * i + h : e] = epoch;
+            if (drop_nonfinite<ST>(v, r, h))
+                set_mark(cell[a.L == 1 ? (2 * j + (r >> 1)) * 2 * a.bx + 2 * i + h : e], epoch);
 }
 
 // Whether a pixel (in the loaded area's coordinates) depends on a marked one:
@@ -253,7 +262,7 @@ DEV bool depends_on_mark(const PhaseArgs& a, const char* lds, int R, int p, int 
     for (int j = j0; j <= j1; ++j)
 #pragma unroll 1
         for (int i = i0; i <= i1; ++i)
-            if (cell[j * cw + i] == epoch) return true;
+            if (marked(cell[j * cw + i], epoch)) return true;
     return false;
 }
 
@@ -538,7 +547,7 @@ __global__ void __launch_bounds__(kThreads, (phase_waves<K, ST, NR>())) phase_ke
             }
             off += 2 * W;
         }
-        if (__builtin_expect(reinterpret_cast<const uint16_t*>(lds + a.mark_off)[sp] == epoch, 0)) {
+        if (__builtin_expect(marked(reinterpret_cast<const uint16_t*>(lds + a.mark_off)[sp], epoch), 0)) {
             // the plane holds non-finite pixels: NaN for the outputs that see one
             uint32_t o = out_off;
 #pragma unroll 1

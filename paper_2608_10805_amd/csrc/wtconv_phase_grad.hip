@@ -166,7 +166,7 @@ DEV void put_side(const PhaseSide& g, int L, int w2, char* plane, int y0, int x0
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            s1[i][j] = 0.25f * ((v[2 * i][2 * j] + v[2 * i][2 * j + 1]) + (v[2 * i + 1][2 * j] + v[2 * i + 1][2 * j + 1]));
+            s1[i][j] = mean4(v[2 * i][2 * j], v[2 * i][2 * j + 1], v[2 * i + 1][2 * j], v[2 * i + 1][2 * j + 1]);
         uint32_t h, m, l;
         split2(s1[i][0], s1[i][1], h, m, l);
         char* q = plane + g.off[1] + 2 * (((y0 >> 1) + i + M) * g.pitch[1] + (x0 >> 1) + M);
@@ -175,7 +175,7 @@ DEV void put_side(const PhaseSide& g, int L, int w2, char* plane, int y0, int x0
         *reinterpret_cast<uint32_t*>(q + 2 * g.psz[1]) = l;
     }
     if (L < 3) return;
-    const float s2 = 0.25f * ((s1[0][0] + s1[0][1]) + (s1[1][0] + s1[1][1]));
+    const float s2 = mean4(s1[0][0], s1[0][1], s1[1][0], s1[1][1]);
     uint32_t h, m, l;
     split2(s2, 0.f, h, m, l);
     uint16_t* q = reinterpret_cast<uint16_t*>(plane + g.off[2]) + ((y0 >> 2) + M) * g.pitch[2] + (x0 >> 2) + M;
@@ -199,7 +199,7 @@ DEV void deepen_side(const PhaseGradArgs& a, const PhaseSide& g, char* lds, int 
         const bool bx = 2 * i + 1 < pw, by = 2 * j + 1 < ph;
         const float v00 = src[0], v01 = bx ? src[1] : 0.f;
         const float v10 = by ? src[pw] : 0.f, v11 = (bx && by) ? src[pw + 1] : 0.f;
-        const float v = 0.25f * ((v00 + v01) + (v10 + v11));
+        const float v = mean4(v00, v01, v10, v11);
         if (s + 1 < a.L) reinterpret_cast<float*>(plane + g.mf[s])[j * w + i] = v;
         uint32_t hh, m, l;
         split2(v, 0.f, hh, m, l);

@@ -71,6 +71,38 @@ def test_non_finite_pixels_reach_their_outputs_only(B, C, H, W, k, L, dtype, val
     assert torch.equal(got[keep], want[keep])
 
 
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", [(4, 768, 56, 56, 5, 1, "f32"), (4, 768, 56, 56, 5, 3, "bf16"),
+                                               (4, 768, 28, 60, 3, 2, "f16"), (6, 256, 130, 128, 5, 1, "bf16")])
+def test_non_finite_planes_one_after_another(B, C, H, W, k, L, dtype):
+    """A workgroup's wavefronts store one batch of planes while others load the
+    next: with nothing but NaN in all of them, every output is NaN."""
+    _, dev = setup(1, C, 8, 8, k, L, dtype, seed=5)
+    x = torch.full((B, C, H, W), float("nan"), dtype=dev.x.dtype, device=dev.x.device)
+    y = binding.forward(x, dev.bw, dev.bs, dev.lw, dev.ls)
+    assert bool(torch.isnan(y).all())
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", [(3, 2, 56, 56, 5, 1, "f32"), (2, 2, 56, 56, 5, 3, "f32"),
+                                               (2, 2, 40, 41, 5, 2, "bf16"), (2, 2, 28, 28, 5, 5, "bf16"),
+                                               (5, 2, 28, 28, 3, 3, "f16"), (2, 1, 130, 128, 5, 1, "f32")])
+def test_lowest_values_reach_their_outputs_only(B, C, H, W, k, L, dtype):
+    """Pixels of the type's lowest value (a mask's): finite outputs, those that
+    depend on one as the oracle has them, the others the same bits as without."""
+    inp, dev = setup(B, C, H, W, k, L, dtype, seed=11)
+    clean, bad = dev.x.clone(), np.zeros((B, C, H, W), bool)
+    for b, c, y, x in [(0, 0, H // 3, W // 2 + 1), (B - 1, C - 1, H - 1, 0)]:
+        dev.x[b, c, y, x] = torch.finfo(dev.x.dtype).min
+        clean[b, c, y, x] = 0
+        bad[b, c] |= footprint(H, W, y, x, k, L)
+    got = dev.forward()
+    assert bool(torch.isfinite(got).all())
+    want = binding.forward(clean, dev.bw, dev.bs, dev.lw, dev.ls)
+    keep = torch.from_numpy(~bad).to(got.device)
+    assert torch.equal(got[keep], want[keep])
+    ref = oracle.forward(to_np(dev.x), inp.base_w, inp.base_scale, inp.level_w, inp.level_scale)
+    assert rel_err(to_np(got), ref) < TOL[dtype]
+
+
 GRADIENT = [
     (1, 1, 9, 4, 5, 1, "bf16"), (3, 2, 11, 9, 3, 1, "f16"), (5, 2, 16, 17, 5, 2, "bf16"), (34, 1, 14, 14, 5, 2, "bf16"),
     (2, 2, 31, 33, 5, 3, "f16"), (3, 1, 57, 55, 5, 3, "bf16"), (3, 2, 48, 48, 5, 5, "bf16"), (19, 2, 14, 14, 3, 3, "bf16"),
