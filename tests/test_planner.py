@@ -139,6 +139,37 @@ def test_mixed_round_plans_hold_their_invariants(mixed_check):
     assert sum(o.startswith("ok") for o in out) > 1000
 
 
+@pytest.fixture(scope="module")
+def phase_check(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("needs g++")
+    exe = str(tmp_path_factory.mktemp("phase") / "phase_check")
+    subprocess.run([gxx, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "c++",
+                    os.path.join(ROOT, "tests", "planner", "phase_check.cpp"), "-o", exe,
+                    "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True,
+                   capture_output=True)
+    return exe
+
+
+def test_polyphase_plans_hold_their_invariants(phase_check):
+    """Every polyphase plan (whole plane, regions, kernel gradients) over 3000
+    seeded random problems stays inside its arrays and the LDS and covers the
+    plane and the batch (tests/planner/phase_check.cpp)."""
+    rng = random.Random(11)
+    size = lambda hi: int(round(2 ** rng.uniform(2, hi)))  # noqa: E731
+    lines = [f"{size(8.5) - 3} {size(10) - 3} {size(8.5) - 3} {size(8.5)} {rng.choice([3, 5])} {rng.randint(1, 5)} "
+             f"{rng.randint(0, 2)}" for _ in range(3000)]
+    lines += [f"{B} {C} {n} {n} {k} {L} {t}" for B, C, n in ((64, 96, 56), (128, 384, 14), (70000, 1, 8), (16, 64, 224))
+              for k in (3, 5) for L in range(1, 6) for t in range(3)]
+    out = subprocess.run([phase_check], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True,
+                         timeout=120).stdout.split("\n")[:len(lines)]
+    fails = [(l, o) for l, o in zip(lines, out) if not o.startswith("ok")]
+    assert not fails, fails[:5]
+    assert all(sum(o.split()[i] == "1" for o in out) > 800 for i in (1, 2, 3))
+
+
 def test_odd_shape_block_rounds(planner):
     """63 x 95 planes have 384 4x4 blocks: the gradient pass takes them in
     two rounds over one resident plane."""
