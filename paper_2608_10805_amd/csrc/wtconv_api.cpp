@@ -1498,13 +1498,19 @@ bool make_phase_region_plan(const wtconv_desc& d, PhasePlan& out)
 //    128 x 128 (0.79-0.90) and 96 x 96 (0.89-0.96), not on 224 x 224 (a
 //    training step 1.01-1.04); at k = 3 it is the other way round (224 x 224
 //    0.95-0.98, 96 x 96 L3 1.11).
+bool phase_f32_tiles_pay(const wtconv_desc& d)
+{
+    const int edge = std::max(d.H, d.W);
+    return d.k == 3 ? edge >= 112 : edge <= 160;
+}
+
 bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
 {
     if (e.kind == PhaseExec::None) return false;
     const int edge = std::max(d.H, d.W);
     if (e.kind == PhaseExec::Region)
         return choose(d, false).mode == Mode::Region &&
-               (d.dtype != WTCONV_F32 || d.L < 2 || (d.k == 3 ? edge >= 112 : edge <= 160));
+               (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d));
     const wtc::PhaseArgs& a = e.pl.a;
     if (d.L >= 2 && a.PP == 1 && 2 * a.bx * a.by < wtc::kThreads) return false;
     if (d.dtype == WTCONV_F32) return d.L <= 2 || (d.L == 3 && (d.k == 3 || edge > 32));
@@ -1513,10 +1519,19 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
 }
 
 // region: always in region tiles (a pass on the first level with a carry).
-PhaseExec choose_phase(const wtconv_desc& d, bool region = false)
+// skip_base: a coarse sub-problem, without the base path.
+PhaseExec choose_phase(const wtconv_desc& d, int skip_base, bool region = false)
 {
     PhaseExec none;
     if (!wtc::launch_phase_forward || (d.k != 3 && d.k != 5) || d.L < 1 || d.W < 4) return none;
+    // Without the base path the vector kernels have half the FMAs, while the
+    // weight matrix is as large as with it: in float32 the vector kernels stay
+    // (56 x 56 B16 C64 L1 sub-problem 13.1 us, polyphase 16.1; 224 x 224 B16 C64
+    // L3 training step 821 us, with polyphase sub-problems 862). In 16 bits the
+    // polyphase ones win (256 x 256 B8 C128 L3 f16 forward 203 us, vector
+    // sub-problems 250; backward 382, 443).
+    if (skip_base && d.dtype == WTCONV_F32) return none;
+    if (region && d.dtype == WTCONV_F32 && !phase_f32_tiles_pay(d)) return none;
     // Planes of at most 8 x 8 have the one-plane-per-lane kernel. At L = 1 in 16
     // bits the polyphase one is faster on rows of whole vectors (8 x 8 B128 C768
     // 18.5 -> 13.7 us) and where 64 planes per wavefront leave the chip idle
@@ -1558,23 +1573,23 @@ size_t pass_partial_bytes(const wtconv_desc& d, const Exec& ex)
 // Workspace layouts.
 //   forward:  [X_m][carry][sub-problem]                   (split / region with a coarse part)
 //   backward: [partials][X_m][dY_m][dX_m][sub-problem]
-size_t forward_ws(const wtconv_desc& d)
+size_t forward_ws(const wtconv_desc& d, int skip_base)
 {
-    const PhaseExec pe = choose_phase(d);
+    const PhaseExec pe = choose_phase(d, skip_base);
     if (pe.kind != PhaseExec::None) {
         if (pe.kind == PhaseExec::Resident || d.L < 2) return 0;
-        const size_t sub = forward_ws(coarse_desc(d, 1));
+        const size_t sub = forward_ws(coarse_desc(d, 1), 1);
         return sub == kUnsupported ? sub : 2 * level_bytes(d, 1) + sub;
     }
     const Exec ex = choose(d, false);
     if (ex.mode == Mode::None) return kUnsupported;
     if (!ex.coarse) return 0;
-    const size_t sub = forward_ws(coarse_desc(d, ex.m));
+    const size_t sub = forward_ws(coarse_desc(d, ex.m), 1);
     if (sub == kUnsupported) return kUnsupported;
     return 2 * level_bytes(d, ex.m) + sub;
 }
 
-size_t backward_ws(const wtconv_desc& d);
+size_t backward_ws(const wtconv_desc& d, int skip_base);
 
 // Gradient-pass workspace: [partials][X_m][dY_m][coarse backward][forward workspace of dx]
 size_t grad_partial_bytes(const wtconv_desc& d, const GradExec& ge)
@@ -1609,17 +1624,17 @@ bool dx_pass_plan(const wtconv_desc& d, int m, Plan& pl)
 size_t grad_coarse_bytes(const wtconv_desc& d, const GradExec& ge)
 {
     if (!ge.coarse) return 0;
-    const size_t sub = backward_ws(coarse_desc(d, ge.Lf));
+    const size_t sub = backward_ws(coarse_desc(d, ge.Lf), 1);
     if (sub == kUnsupported) return kUnsupported;
     return 3 * level_bytes(d, ge.Lf) + sub;
 }
 
-size_t backward_ws(const wtconv_desc& d)
+size_t backward_ws(const wtconv_desc& d, int skip_base)
 {
     const GradExec ge = choose_grad(d);
     if (ge.use) {
         const size_t coarse = grad_coarse_bytes(d, ge);
-        const size_t fwd = forward_ws(d);
+        const size_t fwd = forward_ws(d, skip_base);
         if (coarse == kUnsupported || fwd == kUnsupported) return kUnsupported;
         return grad_partial_bytes(d, ge) + coarse + fwd;
     }
@@ -1627,7 +1642,7 @@ size_t backward_ws(const wtconv_desc& d)
     if (ex.mode == Mode::None) return kUnsupported;
     const size_t part = pass_partial_bytes(d, ex);
     if (!ex.coarse) return part;
-    const size_t sub = backward_ws(coarse_desc(d, ex.m));
+    const size_t sub = backward_ws(coarse_desc(d, ex.m), 1);
     if (sub == kUnsupported) return kUnsupported;
     return part + 3 * level_bytes(d, ex.m) + sub;
 }
@@ -1797,7 +1812,7 @@ wtconv_status phase_pass(const wtconv_desc& d, const PhaseExec& pe, const void* 
 wtconv_status forward_impl(const wtconv_desc& d, const void* x, const wtc::ParamPtrs& p, void* y, char* ws,
                            int skip_base, hipStream_t stream, FinJob* fin = nullptr)
 {
-    const PhaseExec pe = choose_phase(d);
+    const PhaseExec pe = choose_phase(d, skip_base);
     if (pe.kind != PhaseExec::None) {
         const void* carry = nullptr;
         if (pe.kind == PhaseExec::Region && d.L >= 2) {
@@ -1965,7 +1980,7 @@ wtconv_status region_grad_backward(const wtconv_desc& d, const Exec& ex, const G
     pr.b0 = nullptr;  // the bias does not reach dx
     wtconv_desc f = d;
     f.L = 1;
-    const PhaseExec pe = choose_phase(f, dx1 != nullptr);
+    const PhaseExec pe = choose_phase(f, skip_base, dx1 != nullptr);
     if (pe.kind != PhaseExec::None) return phase_pass(f, pe, dy, pr, dx, skip_base, dx1, stream, nullptr);
     const Exec fx = choose(f, false);
     if (fx.mode != Mode::Region && fx.mode != Mode::Resident) return WTCONV_ERR_UNSUPPORTED;
@@ -1999,7 +2014,8 @@ wtconv_status partials_impl(const wtconv_desc& d, const void* x, const void* dy,
         Plan dxp;
         // (A polyphase forward takes every level of the plane in its one launch
         // and needs no such carry.)
-        const bool dx_carry = dx && ge.coarse && choose_phase(d).kind != PhaseExec::Resident && dx_pass_plan(d, ge.Lf, dxp);
+        const bool dx_carry = dx && ge.coarse && choose_phase(d, skip_base).kind != PhaseExec::Resident &&
+                              dx_pass_plan(d, ge.Lf, dxp);
         wtconv_status st = WTCONV_OK;
         void* dx1 = nullptr;
         if (ge.coarse) {
@@ -2162,7 +2178,7 @@ wtconv_status backward_checks(const wtconv_desc* desc, const void* x, const void
     const wtconv_desc& d = *desc;
     if (!x || !dy || !base_w || !base_scale) return WTCONV_ERR_NULL;
     if ((st = check_levels(d.L, level_w, level_scale)) != WTCONV_OK) return st;
-    const size_t need = backward_ws(d);
+    const size_t need = backward_ws(d, 0);
     if ((st = check_workspace(need, workspace, workspace_bytes)) != WTCONV_OK) return st;
     if (need == 0) return WTCONV_ERR_WORKSPACE;  // the backward always writes partials
     const size_t act = (size_t)d.B * d.C * d.H * d.W * elem_size(d.dtype);
@@ -2224,7 +2240,7 @@ const char* wtconv_status_string(wtconv_status s)
 size_t wtconv_forward_workspace_bytes(const wtconv_desc* desc)
 {
     if (check_desc(desc) != WTCONV_OK) return 0;
-    const size_t n = forward_ws(*desc);
+    const size_t n = forward_ws(*desc, 0);
     return n == kUnsupported ? 0 : n;
 }
 
@@ -2238,7 +2254,7 @@ wtconv_status wtconv_forward(const wtconv_desc* desc, const void* x, const float
     const wtconv_desc& d = *desc;
     if (!x || !y || !base_w || !base_scale) return WTCONV_ERR_NULL;
     if ((st = check_levels(d.L, level_w, level_scale)) != WTCONV_OK) return st;
-    const size_t need = forward_ws(d);
+    const size_t need = forward_ws(d, 0);
     if ((st = check_workspace(need, workspace, workspace_bytes)) != WTCONV_OK) return st;
     const size_t bytes = (size_t)d.B * d.C * d.H * d.W * elem_size(d.dtype);
     Range ins[5 + 2 * kMaxLevels];
@@ -2255,7 +2271,7 @@ wtconv_status wtconv_forward(const wtconv_desc* desc, const void* x, const float
 size_t wtconv_backward_workspace_bytes(const wtconv_desc* desc)
 {
     if (check_desc(desc) != WTCONV_OK) return 0;
-    const size_t n = backward_ws(*desc);
+    const size_t n = backward_ws(*desc, 0);
     return n == kUnsupported ? 0 : n;
 }
 
@@ -2287,7 +2303,7 @@ wtconv_status wtconv_backward_finalize(const wtconv_desc* desc, const float* bas
     if ((st = check_levels(d.L, level_w, level_scale)) != WTCONV_OK) return st;
     if ((st = check_levels(d.L, (const float* const*)d_level_w, (const float* const*)d_level_scale)) != WTCONV_OK)
         return st;
-    const size_t need = backward_ws(d);
+    const size_t need = backward_ws(d, 0);
     if ((st = check_workspace(need, workspace, workspace_bytes)) != WTCONV_OK) return st;
     if (need == 0) return WTCONV_ERR_WORKSPACE;
     Range ins[4 + 2 * kMaxLevels];
@@ -2306,7 +2322,7 @@ wtconv_status wtconv_backward_finalize(const wtconv_desc* desc, const float* bas
 size_t wtconv_backward_data_workspace_bytes(const wtconv_desc* desc)
 {
     if (check_desc(desc) != WTCONV_OK) return 0;
-    const size_t n = forward_ws(*desc);
+    const size_t n = forward_ws(*desc, 0);
     return n == kUnsupported ? 0 : n;
 }
 
@@ -2320,7 +2336,7 @@ wtconv_status wtconv_backward_data(const wtconv_desc* desc, const void* dy, cons
     const wtconv_desc& d = *desc;
     if (!dy || !dx || !base_w || !base_scale) return WTCONV_ERR_NULL;
     if ((st = check_levels(d.L, level_w, level_scale)) != WTCONV_OK) return st;
-    const size_t need = forward_ws(d);
+    const size_t need = forward_ws(d, 0);
     if ((st = check_workspace(need, workspace, workspace_bytes)) != WTCONV_OK) return st;
     const size_t bytes = (size_t)d.B * d.C * d.H * d.W * elem_size(d.dtype);
     Range ins[5 + 2 * kMaxLevels];

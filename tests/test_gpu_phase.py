@@ -138,3 +138,21 @@ def test_kernel_gradients_bitwise_reproducible():
     a, b = dev.backward(), dev.backward()
     for p, q in zip((a[1], a[2], *a[3], *a[4]), (b[1], b[2], *b[3], *b[4])):
         assert torch.equal(p, q)
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L", [(2, 2, 130, 128, 5, 3), (1, 2, 161, 166, 5, 3), (1, 1, 226, 110, 3, 4)])
+def test_float32_planes_with_a_sub_problem(B, C, H, W, k, L):
+    """float32 planes in region tiles on both sides of the size up to which the
+    tiles run polyphase; the sub-problem below them, without a base path, does
+    not. Forward and combined backward, the operator's float32 tolerance."""
+    inp, dev = setup(B, C, H, W, k, L, "f32", seed=11)
+    want = oracle.forward(inp.x, inp.base_w, inp.base_scale, inp.level_w, inp.level_scale)
+    assert rel_err(to_np(dev.forward()), want) < TOL["f32"]
+    dx, dbw, dbs, dlw, dls = binding.backward(dev.x, dev.dy, dev.bw, dev.bs, dev.lw, dev.ls)
+    torch.cuda.synchronize()
+    ref = oracle.backward(inp.x, inp.dy, inp.base_w, inp.base_scale, inp.level_w, inp.level_scale)
+    for got, name in [(dx, "dx"), (dbw, "d_base_w"), (dbs, "d_base_scale")]:
+        assert rel_err(to_np(got), ref[name]) < TOL["f32"], name
+    for l in range(L):
+        assert rel_err(to_np(dlw[l]), ref["d_level_w"][l]) < TOL["f32"]
+        assert rel_err(to_np(dls[l]), ref["d_level_scale"][l]) < TOL["f32"]
