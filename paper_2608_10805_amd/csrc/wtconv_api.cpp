@@ -1479,6 +1479,18 @@ bool make_phase_region_plan(const wtconv_desc& d, PhasePlan& out)
     return best >= 0;
 }
 
+// float32 region tiles with a carry: the polyphase tiles win where the vector
+// kernels' 56 x 56 tiles are mostly padding (polyphase / vector forward, k = 5
+// and 3: 120 x 120 0.94, 128 x 128 0.81-0.95, with dx 0.93-0.98) and lose where
+// these fit (112 x 112 1.02-1.06, 140 x 140 1.09, 160 x 160 1.03, 224 x 224
+// 1.04). Between them it depends on the batch (100 x 100 0.99 and dx 1.015, 150 x
+// 150 0.94-1.07, 256 x 256 0.98 and dx 1.05): the vector kernels stay.
+bool phase_f32_tiles_pay(const wtconv_desc& d)
+{
+    const long tiled = 56L * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
+    return std::max(d.H, d.W) <= 136 && 10 * tiled >= 17L * d.H * d.W;
+}
+
 // Where the polyphase forward is the faster one. Measured on MI355X against the
 // vector kernels (forward time, polyphase / vector; k = 5 and 3):
 //  - 16-bit storage, L <= 4: 0.30 (63 x 95 L1) to 0.99, most shapes 0.45-0.75;
@@ -1494,16 +1506,7 @@ bool make_phase_region_plan(const wtconv_desc& d, PhasePlan& out)
 //    threads without a block (31 x 47): 1.02-1.4;
 //  - a plane too tall for one workgroup's columns runs in region tiles with a
 //    carrier pass; where the vector kernels hold it whole they are faster at
-//    L >= 2 (84 x 84 1.4-1.9), and in float32 at L >= 2 the tiles win on
-//    128 x 128 (0.79-0.90) and 96 x 96 (0.89-0.96), not on 224 x 224 (a
-//    training step 1.01-1.04); at k = 3 it is the other way round (224 x 224
-//    0.95-0.98, 96 x 96 L3 1.11).
-bool phase_f32_tiles_pay(const wtconv_desc& d)
-{
-    const int edge = std::max(d.H, d.W);
-    return d.k == 3 ? edge >= 112 : edge <= 160;
-}
-
+//    L >= 2 (84 x 84 1.4-1.9); float32 at L >= 2: phase_f32_tiles_pay().
 bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
 {
     if (e.kind == PhaseExec::None) return false;
