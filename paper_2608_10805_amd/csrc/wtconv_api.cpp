@@ -1483,20 +1483,27 @@ bool make_phase_region_plan(const wtconv_desc& d, PhasePlan& out)
 // kernels' 56 x 56 tiles are mostly padding (polyphase / vector forward, k = 5
 // and 3: 120 x 120 0.94, 128 x 128 0.81-0.95, with dx 0.93-0.98) and lose where
 // these fit (112 x 112 1.02-1.06, 140 x 140 1.09, 160 x 160 1.03, 224 x 224
-// 1.04). Between them it depends on the batch (100 x 100 0.99 and dx 1.015, 150 x
+// 1.04) or on planes up to 112 pixels (72 x 72 L3 1.29). Between them it depends on the batch (100 x 100 0.99 and dx 1.015, 150 x
 // 150 0.94-1.07, 256 x 256 0.98 and dx 1.05): the vector kernels stay.
 bool phase_f32_tiles_pay(const wtconv_desc& d)
 {
     const long tiled = 56L * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
-    return std::max(d.H, d.W) <= 136 && 10 * tiled >= 17L * d.H * d.W;
+    const int edge = std::max(d.H, d.W);
+    return edge > 112 && edge <= 136 && 10 * tiled >= 17L * d.H * d.W;
 }
 
 // Where the polyphase forward is the faster one. Measured on MI355X against the
 // vector kernels (forward time, polyphase / vector; k = 5 and 3):
 //  - 16-bit storage, L <= 4: 0.30 (63 x 95 L1) to 0.99, most shapes 0.45-0.75;
-//    float32, L <= 2: 0.61 (128 x 128 L1) to 1.0, most 0.80-0.95; L = 3
-//    0.69-0.95, but at k = 5 on planes up to 32 pixels 0.98-1.07 (in a training
-//    step 28 x 28 1.04);
+//    float32, L = 1:
+//    0.61 (128 x 128) to 0.98, training steps 0.82 to 1.02;
+//  - float32, L = 2 and 3, k = 5 (training steps): the matrix instructions take
+//    as long as the vector kernels' FMAs where these have their lanes full (56 x
+//    56 L2 1.007, L3 1.017 to 1.05 by card, as the gradient pass after it clocks
+//    lower; 64 x 64 1.02, 1.08; 40 x 40 L2 1.037; 32 x 32 L2 1.025), less where
+//    a quarter or more of the 4 x 4 blocks' lanes idle (48 x 48 0.90, 0.89; 63 x
+//    95 0.83, 0.88; 47 x 61 1.006, 0.98) and on the smallest planes (20 x 20 L2
+//    0.95, 14 x 14 L2 0.94); k = 3: 0.93-0.95, two rounds of blocks at L3 1.03;
 //  - float32, L >= 4: 0.84 to 1.8 (its deeper stages need six products per
 //    term and one wavefront runs them);
 //  - 16-bit, L = 5: 56 x 56 0.88, 28 x 28 0.75, 20 x 20 0.78, but 40 x 40 1.08
@@ -1516,7 +1523,14 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
                (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d));
     const wtc::PhaseArgs& a = e.pl.a;
     if (d.L >= 2 && a.PP == 1 && 2 * a.bx * a.by < wtc::kThreads) return false;
-    if (d.dtype == WTCONV_F32) return d.L <= 2 || (d.L == 3 && (d.k == 3 || edge > 32));
+    if (d.dtype == WTCONV_F32) {
+        const int blocks = a.bx * a.by, lanes = ceil_to(blocks, wtc::kThreads);
+        if (d.L == 1) return true;
+        if (d.k == 3) return d.L == 2 || (d.L == 3 && blocks <= wtc::kThreads);
+        const int used = blocks <= wtc::kThreads ? wtc::kThreads / blocks * blocks : blocks;
+        const bool idle = 4 * used <= 3 * lanes;
+        return (d.L == 2 && (idle || edge <= 20)) || (d.L == 3 && idle && edge > 32);
+    }
     if (d.L <= 4) return true;
     return edge >= 48 || (edge <= 32 && (long)d.B * d.C < kSplitMinPlanes);
 }
