@@ -53,11 +53,11 @@ bool modes_active()
            tls.has(c10::DispatchKey::FuncTorchDynamicLayerFrontMode) || tls.has(c10::DispatchKey::Functionalize);
 }
 
-// The problem the arguments describe, if it is the plain case.
+// The problem the arguments describe, if they are plain.
 bool describe(const Tensor& x, const Tensor& bw, const Tensor& bs, const std::optional<Tensor>& bias,
               const variable_list& levels, wtconv_desc& d)
 {
-    if (modes_active() || !x.defined() || !x.is_cuda() || x.dim() != 4 || bw.dim() != 3 || levels.size() % 2) return false;
+    if (!x.defined() || !x.is_cuda() || x.dim() != 4 || bw.dim() != 3 || levels.size() % 2) return false;
     const c10::Device dev = x.device();
     if (!plain(x, dev) || x.numel() == 0) return false;
     if (x.scalar_type() == at::kFloat)
@@ -192,7 +192,7 @@ py::object apply(const Tensor& x, const Tensor& bw, const Tensor& bs, const std:
                  const variable_list& levels)
 {
     wtconv_desc d;
-    if (!forward_fn || !describe(x, bw, bs, bias, levels, d) || backward_bytes(&d) == 0) return py::none();
+    if (!forward_fn || modes_active() || !describe(x, bw, bs, bias, levels, d) || backward_bytes(&d) == 0) return py::none();
     Tensor y;
     try {
         py::gil_scoped_release no_gil;

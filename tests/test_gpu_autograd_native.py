@@ -75,3 +75,26 @@ def test_saved_tensor_hooks_see_the_saved_tensors():
     y = python_path(x, bw, bs, lw, ls, bb)
     want = torch.autograd.grad(y, [x, bw], torch.ones_like(y))
     assert len(seen) == 6 and all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_dispatch_mode_around_the_backward_alone():
+    """A mode that is entered after the forward sees the backward's
+    allocations, as on the Python path; it does not make the call fail."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Count(TorchDispatchMode):
+        n = 0
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.n += 1
+            return func(*args, **(kwargs or {}))
+
+    bw, bs, bb, lw, ls = params(3, 5, 1, True)
+    x = torch.randn(2, 3, 16, 16, device="cuda", requires_grad=True)
+    got = []
+    for fn in (autograd.wtconv, python_path):
+        y = fn(x, bw, bs, lw, ls, bb)
+        with Count() as mode:
+            got.append(torch.autograd.grad(y, [x, bw, bb], torch.ones_like(y)))
+        assert mode.n > 0
+    assert all(torch.equal(a, b) for a, b in zip(*got))
