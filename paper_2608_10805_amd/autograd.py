@@ -7,6 +7,7 @@ import ctypes
 import math
 
 import torch
+import torch.overrides
 
 from . import binding
 
@@ -60,10 +61,11 @@ def _load_native():
 
 def wtconv(x, base_w, base_scale, level_w, level_scale, base_bias=None):
     """The operator under autograd. The plain case (dense, contiguous GPU tensors
-    that fit the problem, nothing tracing or transforming) runs from native
-    code; WTConvFunction does the same for every other one, or raises."""
+    that fit the problem and override no torch function, nothing tracing or
+    transforming) runs from native code; WTConvFunction does the same for every other one, or raises."""
     ext = _native if _native is not None else _load_native()
-    if ext and len(level_w) == len(level_scale) and not torch.compiler.is_compiling():
+    if (ext and len(level_w) == len(level_scale) and not torch.compiler.is_compiling()
+            and not torch.overrides.has_torch_function((x, base_w, base_scale, base_bias, *level_w, *level_scale))):
         try:
             y = ext.apply(x, base_w, base_scale, base_bias, [*level_w, *level_scale])
         except TypeError:  # an argument that is no tensor

@@ -29,8 +29,9 @@ decltype(&wtconv_backward_workspace_bytes) backward_bytes = nullptr;
 decltype(&wtconv_backward) backward_fn = nullptr;
 decltype(&wtconv_status_string) status_string = nullptr;
 
-// A dense GPU tensor without wrappers (functorch, Python subclasses) and
-// without a forward-mode tangent.
+// A dense GPU tensor without wrappers (functorch, subclasses with a dispatch of
+// their own) and without a forward-mode tangent. A subclass without one looks
+// like any tensor here: the caller leaves it to the Python path.
 bool plain(const Tensor& t, c10::Device dev)
 {
     static const c10::DispatchKeySet wrapped(

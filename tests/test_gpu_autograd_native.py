@@ -98,3 +98,47 @@ def test_dispatch_mode_around_the_backward_alone():
             got.append(torch.autograd.grad(y, [x, bw, bb], torch.ones_like(y)))
         assert mode.n > 0
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+class Tagged(torch.Tensor):
+    """A subclass with torch functions of its own and no dispatch."""
+
+
+class Counted(torch.Tensor):
+    calls = 0
+
+    @classmethod
+    def __torch_function__(cls, func, types, args=(), kwargs=None):
+        cls.calls += 1
+        return super().__torch_function__(func, types, args, kwargs)
+
+
+def test_tensor_subclasses_keep_their_type_and_functions():
+    bw, bs, bb, lw, ls = params(3, 5, 1, True)
+    x = torch.randn(2, 3, 16, 16, device="cuda")
+    y = autograd.wtconv(x.as_subclass(Tagged), bw, bs, lw, ls, bb)
+    assert type(y) is Tagged and torch.equal(y.as_subclass(torch.Tensor), autograd.wtconv(x, bw, bs, lw, ls, bb))
+    for i in range(3):  # x, a kernel, a level's kernel
+        t = [x, bw.detach(), lw[0].detach()]
+        t[i] = t[i].as_subclass(Counted)
+        before = Counted.calls
+        autograd.wtconv(t[0], t[1], bs, [t[2]], ls, bb)
+        assert Counted.calls > before
+
+
+def test_torch_function_mode_sees_the_call():
+    from torch.overrides import TorchFunctionMode
+
+    class Names(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            seen.append(func.__name__)
+            return func(*args, **(kwargs or {}))
+
+    bw, bs, bb, lw, ls = params(3, 5, 1, False)
+    x, names = torch.randn(2, 3, 16, 16, device="cuda"), []
+    for fn in (autograd.wtconv, python_path):
+        seen = []
+        with Names():
+            fn(x, bw, bs, lw, ls, bb)
+        names.append(seen)
+    assert "empty_like" in names[1] and "empty_like" in names[0]
