@@ -62,7 +62,9 @@ def _load_native():
 def wtconv(x, base_w, base_scale, level_w, level_scale, base_bias=None):
     """The operator under autograd. The plain case (dense, contiguous GPU tensors
     that fit the problem and override no torch function, nothing tracing or
-    transforming) runs from native code; WTConvFunction does the same for every other one, or raises."""
+    transforming) runs from native code; WTConvFunction does the same for every
+    other one, or raises."""
+    level_w, level_scale = tuple(level_w), tuple(level_scale)  # (any iterable)
     ext = _native if _native is not None else _load_native()
     if (ext and len(level_w) == len(level_scale) and not torch.compiler.is_compiling()
             and not torch.overrides.has_torch_function((x, base_w, base_scale, base_bias, *level_w, *level_scale))):

@@ -94,3 +94,13 @@ def test_raw_calls_need_one_pointer_per_level(call):
             binding.wtconv_backward_finalize(desc, 1, 1, None, full, full, 1, 1, None, short, full, 1, 1, None)
         else:
             binding.wtconv_backward_data(desc, 1, 1, 1, full, None, 1, 1, 1, None)
+
+
+def test_the_autograd_function_takes_levels_from_any_iterable():
+    """Generators and maps reach the checks (a CPU tensor is then refused), like lists."""
+    from paper_2608_10805_amd import autograd
+
+    p = problem()
+    for wrap in (list, tuple, iter, lambda v: (t for t in v), lambda v: map(torch.nn.Parameter, v)):
+        with pytest.raises(ValueError, match="GPU tensor"):
+            autograd.wtconv(p["x"], p["base_w"], p["base_scale"], wrap(p["level_w"]), wrap(p["level_scale"]))
