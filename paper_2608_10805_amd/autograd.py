@@ -65,13 +65,12 @@ def wtconv(x, base_w, base_scale, level_w, level_scale, base_bias=None):
     transforming) runs from native code; WTConvFunction does the same for every
     other one, or raises."""
     level_w, level_scale = tuple(level_w), tuple(level_scale)  # (any iterable)
-    ext = _native if _native is not None else _load_native()
-    if (ext and len(level_w) == len(level_scale) and not torch.compiler.is_compiling()
-            and not torch.overrides.has_torch_function((x, base_w, base_scale, base_bias, *level_w, *level_scale))):
-        try:
-            y = ext.apply(x, base_w, base_scale, base_bias, [*level_w, *level_scale])
-        except TypeError:  # an argument that is no tensor
-            y = None
+    tensors = (x, base_w, base_scale, *level_w, *level_scale) + (() if base_bias is None else (base_bias,))
+    if (not torch.compiler.is_compiling() and len(level_w) == len(level_scale)
+            and all(isinstance(t, torch.Tensor) for t in tensors) and x.is_cuda
+            and not torch.overrides.has_torch_function(tensors)):
+        ext = _native if _native is not None else _load_native()
+        y = ext.apply(x, base_w, base_scale, base_bias, [*level_w, *level_scale]) if ext else None
         if y is not None:
             return y
     return WTConvFunction.apply(x, base_w, base_scale, base_bias, *level_w, *level_scale)

@@ -142,3 +142,20 @@ def test_torch_function_mode_sees_the_call():
             fn(x, bw, bs, lw, ls, bb)
         names.append(seen)
     assert "empty_like" in names[1] and "empty_like" in names[0]
+
+
+def test_a_type_error_of_a_pack_hook_is_raised_at_once():
+    """The forward is not run a second time over it."""
+    bw, bs, bb, lw, ls = params(3, 5, 1, False)
+    x = torch.randn(2, 3, 16, 16, device="cuda", requires_grad=True)
+    calls = []
+
+    def pack(t):
+        calls.append(t.shape)
+        if len(calls) == 1:
+            raise TypeError("pack")
+        return t
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t), pytest.raises(TypeError, match="pack"):
+        autograd.wtconv(x, bw, bs, lw, ls)
+    assert len(calls) == 1
