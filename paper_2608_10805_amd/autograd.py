@@ -23,19 +23,21 @@ class WTConvFunction(torch.autograd.Function):
         x = x.contiguous()
         y = binding.forward(x, base_w, base_scale, level_w, level_scale, bias=base_bias)
         ctx.save_for_backward(x, base_w, base_scale, base_bias, *level_params)
-        ctx.L = L
         return y
 
     @staticmethod
     def backward(ctx, dy):
         x, base_w, base_scale, base_bias, *level_params = ctx.saved_tensors
-        L = ctx.L
-        need_dbias = base_bias is not None and ctx.needs_input_grad[3]
-        out = binding.backward(x, dy.contiguous(), base_w, base_scale, level_params[:L], level_params[L:],
-                               need_dx=ctx.needs_input_grad[0], bias=base_bias, need_dbias=need_dbias)
-        dx, dbw, dbs, dlw, dls = out[:5]
-        dbb = out[5] if need_dbias else None
-        return (dx, dbw, dbs, dbb, *dlw, *dls)
+        return _backward(x, dy, base_w, base_scale, base_bias, level_params, ctx.needs_input_grad[0],
+                         base_bias is not None and ctx.needs_input_grad[3])
+
+
+def _backward(x, dy, base_w, base_scale, base_bias, level_params, need_dx, need_dbias):
+    L = len(level_params) // 2
+    out = binding.backward(x, dy.contiguous(), base_w, base_scale, level_params[:L], level_params[L:],
+                           need_dx=need_dx, bias=base_bias, need_dbias=need_dbias)
+    dx, dbw, dbs, dlw, dls = out[:5]
+    return (dx, dbw, dbs, out[5] if need_dbias else None, *dlw, *dls)
 
 
 _native = None
@@ -54,7 +56,7 @@ def _load_native():
             lib = binding.load()
             ext.init(*(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value
                        for n in ("wtconv_forward_workspace_bytes", "wtconv_forward",
-                                 "wtconv_backward_workspace_bytes", "wtconv_backward", "wtconv_status_string")))
+                                 "wtconv_backward_workspace_bytes", "wtconv_backward")), _backward)
             _native = ext
     return _native
 

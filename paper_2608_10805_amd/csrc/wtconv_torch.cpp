@@ -11,6 +11,7 @@
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/extension.h>
@@ -27,7 +28,7 @@ decltype(&wtconv_forward_workspace_bytes) forward_bytes = nullptr;
 decltype(&wtconv_forward) forward_fn = nullptr;
 decltype(&wtconv_backward_workspace_bytes) backward_bytes = nullptr;
 decltype(&wtconv_backward) backward_fn = nullptr;
-decltype(&wtconv_status_string) status_string = nullptr;
+PyObject* python_path = nullptr;  // autograd._backward
 
 // A dense GPU tensor without wrappers (functorch, subclasses with a dispatch of
 // their own) and without a forward-mode tangent. A subclass without one looks
@@ -102,6 +103,28 @@ Tensor workspace(size_t bytes, const Tensor& like)
 struct Refused {
 };  // the library refused the forward call
 
+// The Python path's backward, for saved tensors or an upstream gradient that
+// are not the plain case (saved-tensor hooks may hand back others) and for a
+// call that the library refused: it converts them or raises as it does.
+variable_list backward_in_python(const Tensor& x, const Tensor& dy, const Tensor& bw, const Tensor& bs,
+                                 const std::optional<Tensor>& bias, const variable_list& levels, bool need_dx,
+                                 bool need_db)
+{
+    py::gil_scoped_acquire gil;
+    try {
+        const py::object r = py::reinterpret_borrow<py::object>(python_path)(x, dy, bw, bs, bias, levels, need_dx, need_db);
+        variable_list out;
+        for (const py::handle& t : py::reinterpret_borrow<py::tuple>(r))
+            out.push_back(t.is_none() ? Tensor() : t.cast<Tensor>());
+        return out;
+    } catch (py::error_already_set& e) {  // as the autograd engine hands Python errors on
+        e.restore();
+        python_error err;
+        err.persist();
+        throw python_error(std::move(err));
+    }
+}
+
 struct Fn : public torch::autograd::Function<Fn> {
     // (the levels come one by one: autograd takes no list as a differentiable argument)
     template <typename... Levels>
@@ -135,17 +158,15 @@ struct Fn : public torch::autograd::Function<Fn> {
         std::optional<Tensor> bias;
         if (saved[3].defined()) bias = saved[3];
         const variable_list levels(saved.begin() + 4, saved.end());
-        wtconv_desc d;
-        // (saved-tensor hooks may hand back others)
-        TORCH_CHECK(describe(x, bw, bs, bias, levels, d), "wtconv: the saved tensors do not fit the problem");
-        const Tensor dy = grads[0].contiguous();
-        TORCH_CHECK_VALUE(dy.is_cuda() && dy.device() == x.device() && dy.scalar_type() == x.scalar_type() &&
-                              dy.sizes() == x.sizes(),
-                          "dy must have x's shape, dtype and device");
-        const size_t bytes = backward_bytes(&d);
-        TORCH_CHECK(bytes != 0, "no backward plan for this shape");
-        Tensor ws = workspace(bytes, x);
         const bool need_dx = ctx->needs_input_grad(0), need_db = bias && ctx->needs_input_grad(3);
+        wtconv_desc d;
+        size_t bytes = 0;
+        if (describe(x, bw, bs, bias, levels, d)) bytes = backward_bytes(&d);
+        const Tensor dy = bytes ? grads[0].contiguous() : grads[0];
+        if (!bytes || !dy.is_cuda() || dy.device() != x.device() || dy.scalar_type() != x.scalar_type() ||
+            dy.sizes() != x.sizes())
+            return backward_in_python(x, dy, bw, bs, bias, levels, need_dx, need_db);
+        Tensor ws = workspace(bytes, x);
         variable_list out(4 + levels.size());
         if (need_dx) out[0] = at::empty_like(x);
         out[1] = at::empty_like(bw);
@@ -166,7 +187,7 @@ struct Fn : public torch::autograd::Function<Fn> {
             out[2].mutable_data_ptr<float>(), need_db ? out[3].mutable_data_ptr<float>() : nullptr,
             d.L ? dlw : nullptr, d.L ? dls : nullptr, ws.mutable_data_ptr(), bytes,
             c10::hip::getCurrentHIPStream(x.device().index()));
-        TORCH_CHECK(st == WTCONV_OK, "wtconv_backward: ", status_string(st));
+        if (st != WTCONV_OK) return backward_in_python(x, dy, bw, bs, bias, levels, need_dx, need_db);
         return out;
     }
 };
@@ -204,13 +225,14 @@ py::object apply(const Tensor& x, const Tensor& bw, const Tensor& bs, const std:
     return py::cast(y);
 }
 
-void init(uintptr_t fwd_bytes, uintptr_t fwd, uintptr_t bwd_bytes, uintptr_t bwd, uintptr_t status)
+void init(uintptr_t fwd_bytes, uintptr_t fwd, uintptr_t bwd_bytes, uintptr_t bwd, py::object python_backward)
 {
     forward_bytes = reinterpret_cast<decltype(forward_bytes)>(fwd_bytes);
     forward_fn = reinterpret_cast<decltype(forward_fn)>(fwd);
     backward_bytes = reinterpret_cast<decltype(backward_bytes)>(bwd_bytes);
     backward_fn = reinterpret_cast<decltype(backward_fn)>(bwd);
-    status_string = reinterpret_cast<decltype(status_string)>(status);
+    Py_XDECREF(python_path);
+    python_path = python_backward.release().ptr();  // for the life of the process
 }
 
 }  // namespace

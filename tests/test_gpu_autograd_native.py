@@ -159,3 +159,41 @@ def test_a_type_error_of_a_pack_hook_is_raised_at_once():
     with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t), pytest.raises(TypeError, match="pack"):
         autograd.wtconv(x, bw, bs, lw, ls)
     assert len(calls) == 1
+
+
+def test_errors_of_the_backward_are_the_python_path_s(monkeypatch):
+    """Their types too: saved tensors that a hook hands back in another layout
+    or dtype, and a call that the library refuses."""
+    import ctypes
+
+    from paper_2608_10805_amd import binding
+
+    bw, bs, bb, lw, ls = params(3, 5, 1, True)
+    x = torch.randn(2, 3, 16, 16, device="cuda", requires_grad=True)
+    for unpack in (lambda t: t.mT.contiguous().mT if t.dim() == 4 else t, lambda t: t.half() if t.dim() == 3 else t):
+        for fn in (autograd.wtconv, python_path):
+            with torch.autograd.graph.saved_tensors_hooks(lambda t: t, unpack):
+                y = fn(x, bw, bs, lw, ls, bb)
+            with pytest.raises(ValueError, match="contiguous|float32"):
+                y.sum().backward()
+
+    ext, lib = autograd._load_native(), binding.load()
+    refuse = ctypes.CFUNCTYPE(ctypes.c_int)(lambda: 8)  # WTCONV_ERR_UNSUPPORTED, whatever the arguments
+    address = lambda f: ctypes.cast(f, ctypes.c_void_p).value  # noqa: E731
+    try:
+        ext.init(*(address(getattr(lib, n)) for n in ("wtconv_forward_workspace_bytes", "wtconv_forward",
+                                                      "wtconv_backward_workspace_bytes")),
+                 address(refuse), autograd._backward)
+        monkeypatch.setattr(binding, "wtconv_backward", lambda *a: 8)
+        y = autograd.wtconv(x, bw, bs, lw, ls, bb)
+        with pytest.raises(binding.WTConvError) as e:
+            y.sum().backward()
+        assert e.value.status == 8
+        monkeypatch.undo()  # the Python path is served: so is the call
+        y = autograd.wtconv(x, bw, bs, lw, ls, bb)
+        got = torch.autograd.grad(y, [x, bw, bb, *lw], torch.ones_like(y))
+    finally:
+        autograd._native = None
+        autograd._load_native()
+    y = python_path(x, bw, bs, lw, ls, bb)
+    assert all(torch.equal(a, b) for a, b in zip(got, torch.autograd.grad(y, [x, bw, bb, *lw], torch.ones_like(y))))
