@@ -243,6 +243,62 @@ DEV void put_acc(float* cm, const f32x4 (&acc)[2 * K], int lane, bool add)
     }
 }
 
+// Signed sum (band q of the Haar butterfly) of the 2^l x 2^l block (j, i) of a
+// plane, zero-extended, at its true values.
+template <typename ST>
+DEV double block_sum(const ST* __restrict__ plane, int H, int W, int l, int q, int j, int i)
+{
+    const int half = 1 << (l - 1);
+    double sum = 0.0;
+#pragma unroll 1
+    for (int y = j << l; y < min((j + 1) << l, H); ++y)
+#pragma unroll 1
+        for (int x = i << l; x < min((i + 1) << l, W); ++x) {
+            const bool neg = ((q & 1) && (y & half)) != ((q >> 1) && (x & half));
+            const double v = to_f32(plane[(long)y * W + x]);
+            sum += neg ? -v : v;
+        }
+    return sum;
+}
+
+// One kernel-gradient sum of a workgroup in plain arithmetic, over the pixels
+// [ya, ye) x [xa, xe) of nplanes planes: tap (pr, t) of the base kernel (l = 0)
+// or of band q of level l. The matrix products multiply the positions of a tile
+// outside the plane, and every phase of a band, by themselves: an infinity or
+// NaN in x or dy then reaches taps that do not pair with it, and the band's
+// infinities cancel to NaN. A sum that came out non-finite is therefore formed
+// again here. As in the vector kernels, dy meets the zeros around x (but on
+// planes of at most 8 x 8, whose vector kernel skips them). Cold: a thread walks
+// every plane, until its sum is NaN.
+template <int K, typename ST>
+DEV float plain_sum(const ST* __restrict__ x, const ST* __restrict__ dy, int H, int W, int ya, int ye, int xa, int xe,
+                    int nplanes, long step, int l, int q, int pr, int t)
+{
+    constexpr int R = K / 2;
+    const bool halo = H > kTinyMaxEdge || W > kTinyMaxEdge;
+    const int h = (H + (1 << l) - 1) >> l, w = (W + (1 << l) - 1) >> l;
+    const int j0 = ya >> l, j1 = (ye + (1 << l) - 1) >> l, i0 = xa >> l, i1 = (xe + (1 << l) - 1) >> l;
+    double sum = 0.0;
+#pragma unroll 1
+    for (int b = 0; b < nplanes; ++b, x += step, dy += step)
+#pragma unroll 1
+        for (int j = j0; j < j1; ++j) {
+            const int u = j + pr - R;
+            if (sum != sum || (!halo && (u < 0 || u >= h))) continue;
+#pragma unroll 1
+            for (int i = i0; i < i1; ++i) {
+                const int v = i + t - R;
+                const bool in = u >= 0 && u < h && v >= 0 && v < w;
+                if (!in && !halo) continue;
+                const double d = l == 0 ? (double)to_f32(dy[(long)j * W + i]) : block_sum<ST>(dy, H, W, l, q, j, i);
+                double m = 0.0;
+                if (in) m = l == 0 ? (double)to_f32(x[(long)u * W + v]) : block_sum<ST>(x, H, W, l, q, u, v);
+                sum += d * m;
+            }
+        }
+    return (float)sum;
+}
+
 // Wavefronts per SIMD: three, but two for two block rounds on both sides or
 // with two stages' accumulators in one wavefront (L = 4 and 5).
 template <int NR, int ND>
@@ -313,8 +369,6 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
     const int edge = (4 - (W & 3)) & 3;
     const bool ragged = RGN || edge != 0 || (H & 3) != 0;
     const int ye = RGN ? min(oy + a.rg_T, H) : H, xe = RGN ? min(ox + a.rg_T, W) : W;
-    (void)ye;
-    (void)xe;
     auto put = [&](int b0) {
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
@@ -364,6 +418,11 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
     const int NP = partial_floats_per_channel(K, a.L);
     float* dst = a.partial + ((long)ct * C + c) * NP;
     float* cm = reinterpret_cast<float*>(lds);
+    auto finite_or_plain = [&](float v, int l, int q, int pr, int t) {
+        if (__builtin_expect(__builtin_fabsf(v) < __builtin_inff(), 1)) return v;
+        const long first = ((long)b_begin * C + c) * HW;
+        return plain_sum<K, ST>(xs + first, ds + first, H, W, oy, ye, ox, xe, b_end - b_begin, (long)C * HW, l, q, pr, t);
+    };
     // Stage s's matrix gradient in cm -> its kernel gradients. Thread (q, tap):
     // band q of level s + 1; the last k k threads the base taps (stage 0).
     auto project = [&](int s) {
@@ -380,10 +439,11 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
                             sum += neg ? -v : v;
                         }
                 }
-                dst[KK + (4 * s + q) * KK + tap] = __builtin_ldexpf((float)sum, 4 * s);
+                dst[KK + (4 * s + q) * KK + tap] =
+                    finite_or_plain(__builtin_ldexpf((float)sum, 4 * s), s + 1, q, pr, t);
             } else if (s == 0) {
                 for (int m = 0; m < 16; ++m) sum += cm[entry(pr + R + (m >> 3), t + M - R + (m & 7), m)];
-                dst[tap] = a.skip_base ? 0.f : (float)sum;
+                dst[tap] = a.skip_base ? 0.f : finite_or_plain((float)sum, 0, 0, pr, t);
             }
         }
     };

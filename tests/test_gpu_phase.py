@@ -157,3 +157,61 @@ def test_float32_planes_with_a_sub_problem(B, C, H, W, k, L):
     for l in range(L):
         assert rel_err(to_np(dlw[l]), ref["d_level_w"][l]) < TOL["f32"]
         assert rel_err(to_np(dls[l]), ref["d_level_scale"][l]) < TOL["f32"]
+
+
+def haar_bands(v):
+    """[B, C, H, W] -> the four bands of one orthonormal level, [B, C, 4, h, w], zero-extended."""
+    v = torch.nn.functional.pad(v, [0, v.shape[-1] % 2, 0, v.shape[-2] % 2])
+    a, b, c, d = v[..., 0::2, 0::2], v[..., 0::2, 1::2], v[..., 1::2, 0::2], v[..., 1::2, 1::2]
+    return torch.stack([a + b + c + d, a + b - c - d, a - b + c - d, a - b - c + d], 2) / 2
+
+
+def tap_sums(dz, v, k):
+    """sum of dz times v shifted by every tap, over [B, ..., h, w]: v is zero
+    outside its grid, except on planes of at most 8 x 8, where those products
+    are left out."""
+    h, w, R = v.shape[-2], v.shape[-1], k // 2
+    pad = torch.nn.functional.pad(v, [R] * 4)
+    inside = torch.nn.functional.pad(torch.ones_like(v), [R] * 4) > 0
+    out = torch.empty(*v.shape[1:-2], k, k, dtype=v.dtype)
+    for p in range(k):
+        for t in range(k):
+            prod = dz * pad[..., p:p + h, t:t + w]
+            if tap_sums.tiny:
+                prod = torch.where(inside[..., p:p + h, t:t + w], prod, torch.zeros((), dtype=v.dtype))
+            out[..., p, t] = prod.sum((0, -1, -2))
+    return out
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", [
+    (3, 2, 57, 55, 5, 1, "bf16"), (2, 2, 57, 57, 5, 2, "bf16"), (2, 2, 56, 56, 5, 3, "f16"), (20, 3, 13, 19, 3, 1, "bf16"),
+    (19, 2, 14, 14, 3, 3, "bf16"), (3, 2, 48, 48, 5, 5, "bf16"), (2, 1, 129, 131, 5, 1, "f16"), (3, 2, 7, 7, 5, 1, "bf16")])
+@pytest.mark.parametrize("side", ["x", "dy"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), -float("inf")])
+def test_non_finite_values_reach_the_kernel_gradients_that_see_them_only(B, C, H, W, k, L, dtype, side, value):
+    """A non-finite value in the last row and column, and two of them close to
+    each other: infinities keep their sign, taps that pair with none of them
+    keep their values, as the sums over the plane have it in 64 bits."""
+    inp, dev = setup(B, C, H, W, k, L, dtype, seed=2)
+    t = getattr(dev, side)
+    t[B - 1, 0, H - 1, W - 1] = value
+    t[0, C - 1, H // 2, W // 2] = value
+    t[0, C - 1, H // 2, W // 2 - 1] = float("inf")
+    out = dev.backward()
+    torch.cuda.synchronize()
+    tap_sums.tiny = H <= 8 and W <= 8
+    f64 = lambda v: v.double().cpu()  # noqa: E731
+    x, dy = f64(dev.x), f64(dev.dy)
+    pairs = [(out[1], tap_sums(dy, x, k), f64(dev.bs).view(-1, 1, 1))]
+    for l in range(L):
+        bx, bd = haar_bands(x), haar_bands(dy)
+        pairs.append((out[3][l], tap_sums(bd, bx, k).reshape(4 * C, k, k), f64(dev.ls[l]).view(-1, 1, 1)))
+        x, dy = bx[:, :, 0], bd[:, :, 0]
+    for got, sums, scale in pairs:
+        got, want = f64(got), sums * scale
+        assert torch.equal(torch.isfinite(got), torch.isfinite(want))
+        assert torch.equal(torch.nan_to_num(got, 0, 1, -1)[~torch.isfinite(want)],
+                           torch.nan_to_num(want, 0, 1, -1)[~torch.isfinite(want)])
+        keep = torch.isfinite(want)
+        if keep.any():
+            assert rel_err(got[keep].numpy(), want[keep].numpy()) < 1e-5
