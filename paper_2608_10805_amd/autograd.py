@@ -7,7 +7,6 @@ import ctypes
 import math
 
 import torch
-import torch.overrides
 
 from . import binding
 
@@ -43,10 +42,13 @@ def _backward(x, dy, base_w, base_scale, base_bias, level_params, need_dx, need_
 _native = None
 
 
-def _load_native():
+def _load_native(x=None):
     """The native host path (csrc/wtconv_torch.cpp), given the library's entry
-    points; False where it was not built."""
+    points; False where it was not built, and for an x that is no GPU tensor
+    (nothing is loaded for it)."""
     global _native
+    if x is not None and not (isinstance(x, torch.Tensor) and x.is_cuda):
+        return False
     if _native is None:
         try:
             from . import _wtconv_torch as ext
@@ -67,12 +69,9 @@ def wtconv(x, base_w, base_scale, level_w, level_scale, base_bias=None):
     transforming) runs from native code; WTConvFunction does the same for every
     other one, or raises."""
     level_w, level_scale = tuple(level_w), tuple(level_scale)  # (any iterable)
-    tensors = (x, base_w, base_scale, *level_w, *level_scale) + (() if base_bias is None else (base_bias,))
-    if (not torch.compiler.is_compiling() and len(level_w) == len(level_scale)
-            and all(isinstance(t, torch.Tensor) for t in tensors) and x.is_cuda
-            and not torch.overrides.has_torch_function(tensors)):
-        ext = _native if _native is not None else _load_native()
-        y = ext.apply(x, base_w, base_scale, base_bias, [*level_w, *level_scale]) if ext else None
+    ext = _native if _native is not None else _load_native(x)
+    if ext and len(level_w) == len(level_scale) and not torch.compiler.is_compiling():
+        y = ext.apply(x, base_w, base_scale, base_bias, level_w + level_scale)
         if y is not None:
             return y
     return WTConvFunction.apply(x, base_w, base_scale, base_bias, *level_w, *level_scale)

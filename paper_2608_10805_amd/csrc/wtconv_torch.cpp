@@ -8,11 +8,13 @@
 // caller then runs WTConvFunction, which converts, raises or traces as it does.
 // The library's entry points come in as addresses (init), so this module
 // links to torch only.
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 #include <torch/extension.h>
 
@@ -29,10 +31,10 @@ decltype(&wtconv_forward) forward_fn = nullptr;
 decltype(&wtconv_backward_workspace_bytes) backward_bytes = nullptr;
 decltype(&wtconv_backward) backward_fn = nullptr;
 PyObject* python_path = nullptr;  // autograd._backward
+PyTypeObject* parameter_type = nullptr;  // torch.nn.Parameter
 
 // A dense GPU tensor without wrappers (functorch, subclasses with a dispatch of
-// their own) and without a forward-mode tangent. A subclass without one looks
-// like any tensor here: the caller leaves it to the Python path.
+// their own) and without a forward-mode tangent.
 bool plain(const Tensor& t, c10::Device dev)
 {
     static const c10::DispatchKeySet wrapped(
@@ -210,15 +212,33 @@ Tensor run(const Tensor& x, const Tensor& bw, const Tensor& bs, const std::optio
         throw Refused();
 }
 
-py::object apply(const Tensor& x, const Tensor& bw, const Tensor& bs, const std::optional<Tensor>& bias,
-                 const variable_list& levels)
+// A torch.Tensor or torch.nn.Parameter itself: other subclasses may override
+// torch functions without a dispatch key that shows it.
+bool exact_tensor(py::handle t)
 {
+    return Py_TYPE(t.ptr()) == reinterpret_cast<PyTypeObject*>(THPVariableClass) || Py_TYPE(t.ptr()) == parameter_type;
+}
+
+py::object apply(py::handle x, py::handle bw, py::handle bs, py::handle bias, py::sequence levels)
+{
+    if (!forward_fn || at::impl::torch_function_mode_enabled()) return py::none();
+    if (!exact_tensor(x) || !exact_tensor(bw) || !exact_tensor(bs) || !(bias.is_none() || exact_tensor(bias)))
+        return py::none();
+    variable_list lv;
+    lv.reserve(levels.size());
+    for (const py::object& t : levels) {
+        if (!exact_tensor(t)) return py::none();
+        lv.push_back(THPVariable_Unpack(t.ptr()));
+    }
+    const Tensor &xt = THPVariable_Unpack(x.ptr()), &wt = THPVariable_Unpack(bw.ptr()), &st = THPVariable_Unpack(bs.ptr());
+    std::optional<Tensor> bt;
+    if (!bias.is_none()) bt = THPVariable_Unpack(bias.ptr());
     wtconv_desc d;
-    if (!forward_fn || modes_active() || !describe(x, bw, bs, bias, levels, d) || backward_bytes(&d) == 0) return py::none();
+    if (modes_active() || !describe(xt, wt, st, bt, lv, d) || backward_bytes(&d) == 0) return py::none();
     Tensor y;
     try {
         py::gil_scoped_release no_gil;
-        y = run(x, bw, bs, bias, levels);
+        y = run(xt, wt, st, bt, lv);
     } catch (const Refused&) {
         return py::none();  // the Python path raises the library's error
     }
@@ -231,6 +251,8 @@ void init(uintptr_t fwd_bytes, uintptr_t fwd, uintptr_t bwd_bytes, uintptr_t bwd
     forward_fn = reinterpret_cast<decltype(forward_fn)>(fwd);
     backward_bytes = reinterpret_cast<decltype(backward_bytes)>(bwd_bytes);
     backward_fn = reinterpret_cast<decltype(backward_fn)>(bwd);
+    py::object parameter = py::module_::import("torch.nn").attr("Parameter");
+    parameter_type = reinterpret_cast<PyTypeObject*>(parameter.release().ptr());
     Py_XDECREF(python_path);
     python_path = python_backward.release().ptr();  // for the life of the process
 }
