@@ -1321,7 +1321,7 @@ bool phase_layout(const wtconv_desc& d, wtc::PhaseArgs& a)
         if (off > (1L << 24)) return false;
     }
     a.mark_off = tab;
-    tab += ceil_to(2 * a.PP * (1 + (a.L == 1 ? 4 : 1) * a.bx * a.by), 16);
+    tab += ceil_to(2 * (a.PP * (1 + (a.L == 1 ? 4 : 1) * a.bx * a.by) + 1), 16);
     a.planes_off = tab;
     a.plane_bytes = (int)off;
     // stage 0's table and the staged kernels borrow the planes' area

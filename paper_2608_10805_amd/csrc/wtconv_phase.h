@@ -175,6 +175,25 @@ DEV bool nonfinite(const RawBlock<ST>& v)
     }
 }
 
+// Whether a block holds an infinity.
+template <typename ST>
+DEV bool infinite(const RawBlock<ST>& v)
+{
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = 0; i < RawBlock<ST>::NW; ++i) {
+            if constexpr (sizeof(ST) == 4) {
+                any = any || (v.w[r][i] & 0x7fffffffu) == 0x7f800000u;
+            } else {
+                constexpr uint32_t inf = Scheme<ST>::F16 ? 0x7c00 : 0x7f80;
+                any = any || (v.w[r][i] & 0x7fffu) == inf || ((v.w[r][i] >> 16) & 0x7fffu) == inf;
+            }
+        }
+    return any;
+}
+
 // Zero the infinities and NaNs of row r, columns 2 j and 2 j + 1; whether
 // there was one.
 template <typename ST>

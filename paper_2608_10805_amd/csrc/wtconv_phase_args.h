@@ -52,7 +52,7 @@ struct PhaseArgs {
                         // (the third runs stage 1, the fourth the stages from 2 on; L >= 3)
     int planes_off;     // byte offset of the first plane's region in LDS
     int plane_bytes;    // bytes per plane's region
-    int mark_off;       // byte offset of the marks of non-finite pixels
+    int mark_off;       // byte offset of the marks of non-finite pixels (and one of infinities)
     int lds_bytes;
     int bx, by;         // 4 x 4 pixel blocks per row / column of the loaded area
     float r_bx, r_bxy;  // 1 / bx, 1 / (bx * by)

@@ -29,7 +29,9 @@
 // A tile's window holds zeros of the weight matrix next to its taps, and
 // 0 * inf is NaN: a non-finite input pixel would reach every output of the
 // tiles whose window holds it. Such pixels are zeroed and marked as they are
-// loaded, and the outputs that depend on one, and only they, become NaN.
+// loaded, and the outputs that depend on one, and only they, become NaN. Where
+// one was an infinity, the workgroup goes over these outputs once more at its
+// end: an infinity remains where every term of it has the same sign.
 #include "wtconv_phase.h"
 
 namespace wtc {
@@ -232,6 +234,11 @@ DEV void set_mark(uint16_t& m, uint16_t epoch)
 }
 DEV bool marked(uint16_t m, uint16_t epoch) { return (m >> 1) == epoch || m == 2 * (epoch + 1) + 1; }
 DEV int mark_cells(const PhaseArgs& a) { return a.L == 1 ? 4 * a.bx * a.by : a.bx * a.by; }
+// After the marks: whether any batch so far held an infinity.
+DEV uint16_t& infinity_flag(const PhaseArgs& a, char* lds)
+{
+    return reinterpret_cast<uint16_t*>(lds + a.mark_off)[a.PP * (1 + mark_cells(a))];
+}
 
 // Zeroes the non-finite pixels of block e of plane p and marks their cells.
 template <typename ST>
@@ -240,6 +247,7 @@ DEV void mark_block(const PhaseArgs& a, char* lds, int p, int e, uint16_t epoch,
     uint16_t* marks = reinterpret_cast<uint16_t*>(lds + a.mark_off);
     uint16_t* cell = marks + a.PP + p * mark_cells(a);
     set_mark(marks[p], epoch);
+    if (infinite<ST>(v)) infinity_flag(a, lds) = 1;
     const int j = fdiv(e, a.r_bx), i = e - j * a.bx;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -264,6 +272,123 @@ DEV bool depends_on_mark(const PhaseArgs& a, const char* lds, int R, int p, int 
         for (int i = i0; i <= i1; ++i)
             if (marked(cell[j * cw + i], epoch)) return true;
     return false;
+}
+
+// Terms of the operator that pixel (py, px) of value f (an infinity or NaN)
+// adds to output (y, x), as the vector kernels multiply and add them: bit 0,
+// +inf among them; bit 1, -inf; both, NaN.
+template <int K>
+DEV int nonfinite_terms(const PhaseArgs& a, int c, float f, int py, int px, int y, int x)
+{
+    constexpr int R = K / 2, KK = K * K;
+    int cls = 0;
+    auto add = [&](const float* w, const float* s, int dy, int dx, bool neg) {
+        const int tap = (dy + R) * K + dx + R;
+        const float g = *s * w[a.p.rot ? KK - 1 - tap : tap], t = (neg ? -g : g) * f;
+        cls |= (t < 0.f ? 0 : 1) | (t > 0.f ? 0 : 2);
+    };
+    auto within = [](int dy, int dx) { return dy >= -R && dy <= R && dx >= -R && dx <= R; };
+    if (!a.skip_base && within(py - y, px - x)) add(a.p.w0 + (long)c * KK, a.p.s0 + c, py - y, px - x, false);
+#pragma unroll 1
+    for (int l = 1; l <= a.L; ++l) {
+        const int dy = (py >> l) - (y >> l), dx = (px >> l) - (x >> l);
+        if (!within(dy, dx)) continue;
+        const bool ny = ((py ^ y) >> (l - 1)) & 1, nx = ((px ^ x) >> (l - 1)) & 1;
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q)
+            add(a.p.lw[l - 1] + (long)(4 * c + q) * KK, a.p.ls[l - 1] + 4 * c + q, dy, dx, ((q & 1) && ny) != ((q >> 1) && nx));
+    }
+    return cls;
+}
+
+// Whether every folded weight of channel c is finite.
+template <int K>
+DEV bool finite_weights(const PhaseArgs& a, int c, int lane)
+{
+    constexpr int KK = K * K;
+    bool ok = true;
+#pragma unroll 1
+    for (int e = lane; e < (1 + 4 * a.L) * KK; e += 64) {
+        const int r = e / KK, t = e - r * KK, ch = 4 * c + ((r + 3) & 3);
+        const float g = r == 0 ? a.p.s0[c] * a.p.w0[(long)c * KK + t]
+                               : a.p.ls[(r - 1) / 4][ch] * a.p.lw[(r - 1) / 4][(long)ch * KK + t];
+        ok = ok && __builtin_fabsf(g) < __builtin_inff();
+    }
+    return __ballot(!ok) == 0;
+}
+
+// The wavefront's outputs that became NaN over the planes of its workgroup: an
+// infinity where all their non-finite terms, bias and carry included, have one
+// sign. The wavefront reads 64 pixels at a time. Everything is formed anew from
+// the arguments, so that the kernel keeps nothing through its loop for this.
+template <int K, typename ST, bool RGN>
+DEV void restore_infinities(const PhaseArgs& a, int wave)
+{
+    const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const int bid = (int)blockIdx.x - a.fin_blocks, c = bid % a.C;
+    if (!finite_weights<K>(a, c, lane)) return;
+    const int ntiles = RGN ? a.rg_ntx * a.rg_nty : 1, chunk = (bid / a.C) / ntiles, tile = (bid / a.C) - chunk * ntiles;
+    const int b_begin = chunk * a.nb, b_end = min(a.B, b_begin + a.nb);
+    const int oy = RGN ? (tile / a.rg_ntx) * a.rg_th : 0, ox = RGN ? (tile % a.rg_ntx) * a.rg_tw : 0;
+    const int ye = RGN ? min(oy + a.rg_th, a.H) : a.H, xe = RGN ? min(ox + a.rg_tw, a.W) : a.W;
+    const int y0 = RGN ? max(oy - 4, 0) : 0, y1 = RGN ? min(ye + 4, a.H) : a.H;  // rows that reach the outputs
+    // this lane's outputs, as in the kernel
+    const PhaseStage& g = a.st[0];
+    const int slot = wave * 16 + (lane & 15), vct = g.V * g.ct, sp = slot < a.PP * vct ? slot / vct : -1;
+    const int sv = (slot % vct) / g.ct, I = slot % g.ct, x = ox + 8 * I + 4 * ((lane >> 4) & 1);
+    const int y = oy + 2 * sv * g.js + (lane >> 5), nj = min(max((ye - y + 1) >> 1, 0), g.js);
+    const float bias = (!a.skip_base && a.p.b0) ? a.p.s0[c] * a.p.b0[c] : 0.f;
+    const long HW = (long)a.H * a.W;
+    const int L = a.L;
+#pragma unroll 1
+    for (int b = b_begin; b < b_end; ++b) {
+        const long pl = (long)b * a.C + c;
+        const ST* ip = reinterpret_cast<const ST*>(a.in) + pl * HW;
+        ST* op = reinterpret_cast<ST*>(a.out) + pl * HW;
+        const int n = (b - b_begin) % a.PP == sp ? 4 * nj : 0;
+        uint32_t open = 0, pos = 0, neg = 0;  // bit e: output e is NaN; has a term +inf, -inf
+#pragma unroll 1
+        for (int e = 0; e < n; ++e) {
+            const int yy = y + 2 * (e >> 2), xx = x + (e & 3);
+            if (xx >= xe || to_f32(op[(long)yy * a.W + xx]) == to_f32(op[(long)yy * a.W + xx])) continue;
+            open |= 1u << e;
+            float extra = bias;
+            if (RGN && a.carry)
+                extra += 0.5f * to_f32(reinterpret_cast<const ST*>(a.carry)[(pl * a.carry_H + (yy >> 1)) * a.carry_W + (xx >> 1)]);
+            if (!(extra < __builtin_inff())) pos |= 1u << e;
+            if (!(extra > -__builtin_inff())) neg |= 1u << e;
+        }
+#pragma unroll 1
+        for (long i0 = (long)y0 * a.W; i0 < (long)y1 * a.W && __ballot((open & ~(pos & neg)) != 0) != 0; i0 += 64) {
+            const float f = i0 + lane < (long)y1 * a.W ? to_f32(ip[i0 + lane]) : 0.f;
+            uint64_t m = __ballot(!(__builtin_fabsf(f) < __builtin_inff()));
+#pragma unroll 1
+            for (; m != 0; m &= m - 1) {
+                const int k = __builtin_ctzll(m), py = (int)((i0 + k) / a.W), px = (int)(i0 + k - (long)py * a.W);
+                const float v = __shfl(f, k, 64);
+                // the outputs it reaches: those whose 2^L x 2^L block is within k / 2 of its own
+                const int yl = max(((((py >> L) - K / 2) << L) - y + 1) >> 1, 0);
+                const int yh = min((((((py >> L) + K / 2 + 1) << L) - 1) - y) >> 1, 7);
+                const int xl = max((((px >> L) - K / 2) << L) - x, 0), xh = min((((px >> L) + K / 2 + 1) << L) - 1 - x, 3);
+                uint32_t left = 0;
+                if (yl <= yh && xl <= xh)
+                    left = open & ~(pos & neg) & (~0u << 4 * yl) & (~0u >> (28 - 4 * yh)) &
+                           (0x11111111u * ((0xfu << xl) & (0xfu >> (3 - xh))));
+#pragma unroll 1
+                for (; left != 0; left &= left - 1) {
+                    const int e = __builtin_ctz(left), cls = nonfinite_terms<K>(a, c, v, py, px, y + 2 * (e >> 2), x + (e & 3));
+                    pos |= (uint32_t)(cls & 1) << e;
+                    neg |= (uint32_t)(cls >> 1) << e;
+                }
+            }
+        }
+#pragma unroll 1
+        for (uint32_t left = open & (pos ^ neg); left != 0; left &= left - 1) {
+            const int e = __builtin_ctz(left);
+            op[(long)(y + 2 * (e >> 2)) * a.W + x + (e & 3)] =
+                from_f32<ST>((pos >> e) & 1 ? __builtin_inff() : -__builtin_inff());
+        }
+    }
 }
 
 // Wavefronts per SIMD: three (168 registers) but for float32 k = 5 with two block
@@ -558,6 +683,9 @@ __global__ void __launch_bounds__(kThreads, (phase_waves<K, ST, NR>())) phase_ke
             }
         }
     }
+    const PhaseArgs* ap = (const PhaseArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ap));
+    if (__builtin_expect(infinity_flag(*ap, lds), 0)) restore_infinities<K, ST, RGN>(*ap, wave);
 }
 
 template <int K, typename ST, int NR, bool RGN, bool DEEP>

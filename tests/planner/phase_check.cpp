@@ -84,7 +84,7 @@ static const char* check_forward(const wtconv_desc& d, const PhasePlan& pp)
         }
     }
     REQUIRE(end <= a.plane_bytes);
-    REQUIRE(a.planes_off >= a.mark_off + 2L * a.PP * (1 + (a.L == 1 ? 4 : 1) * a.bx * a.by));
+    REQUIRE(a.planes_off >= a.mark_off + 2L * (a.PP * (1 + (a.L == 1 ? 4 : 1) * a.bx * a.by) + 1));
     REQUIRE(a.planes_off + (long)a.PP * a.plane_bytes <= a.lds_bytes && a.lds_bytes <= 160 * 1024);
     return nullptr;
 }

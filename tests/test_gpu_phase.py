@@ -215,3 +215,62 @@ def test_non_finite_values_reach_the_kernel_gradients_that_see_them_only(B, C, H
         keep = torch.isfinite(want)
         if keep.any():
             assert rel_err(got[keep].numpy(), want[keep].numpy()) < 1e-5
+
+
+def plain_forward(x, bw, bs, lw, ls):
+    """The operator in 64 bits, step by step, with IEEE infinities and NaN."""
+    def conv(v, w):
+        h, wd, k = v.shape[-2], v.shape[-1], w.shape[-1]
+        out = torch.zeros_like(v)
+        for p in range(k):
+            for t in range(k):
+                y0, x0 = p - k // 2, t - k // 2
+                ys, xs = slice(max(0, -y0), h - max(0, y0)), slice(max(0, -x0), wd - max(0, x0))
+                yi, xi = slice(max(0, y0), h + min(0, y0)), slice(max(0, x0), wd + min(0, x0))
+                if ys.start < ys.stop and xs.start < xs.stop:  # (the zeros around a plane meet finite kernels only)
+                    out[..., ys, xs] += v[..., yi, xi] * w[..., p, t, None, None]
+        return out
+
+    bands, sizes, v = [], [], x
+    for _ in lw:
+        sizes.append(v.shape[-2:])
+        bands.append(haar_bands(v))
+        v = bands[-1][:, :, 0]
+    r = None
+    for b, w, s, (h, wd) in reversed(list(zip(bands, lw, ls, sizes))):
+        z = conv(b, (w * s.view(-1, 1, 1)).view(x.shape[1], 4, *w.shape[-2:]))
+        if r is not None:
+            z[:, :, 0] += r
+        ll, lh, hl, hh = z.unbind(2)
+        out = z.new_empty(*z.shape[:2], 2 * z.shape[-2], 2 * z.shape[-1])
+        out[..., 0::2, 0::2], out[..., 0::2, 1::2] = (ll + lh + hl + hh) / 2, (ll + lh - hl - hh) / 2
+        out[..., 1::2, 0::2], out[..., 1::2, 1::2] = (ll - lh + hl - hh) / 2, (ll - lh - hl + hh) / 2
+        r = out[..., :h, :wd]
+    return conv(x, bw * bs.view(-1, 1, 1)) + r
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", [
+    (3, 2, 57, 55, 5, 1, "f32"), (2, 2, 48, 48, 5, 2, "f32"), (2, 2, 57, 57, 5, 2, "bf16"), (2, 2, 56, 56, 5, 3, "bf16"),
+    (3, 2, 56, 56, 5, 2, "f16"), (20, 3, 13, 19, 3, 4, "bf16"), (2, 1, 130, 128, 5, 1, "bf16"), (2, 2, 120, 160, 3, 3, "f16")])
+def test_infinities_keep_their_sign(B, C, H, W, k, L, dtype):
+    """y and dx where a pixel is infinite, and two of opposite sign are close:
+    +inf, -inf or NaN as the step-by-step operator has it. (Level kernels
+    without negative taps: the infinity of some outputs then survives.)"""
+    inp, dev = setup(B, C, H, W, k, L, dtype, seed=9)
+    for w in dev.lw:
+        w.abs_()
+    inf = float("inf")
+    f64 = lambda v: v.double().cpu()  # noqa: E731
+    params = f64(dev.bw), f64(dev.bs), [f64(w) for w in dev.lw], [f64(s) for s in dev.ls]
+    rotated = params[0].flip(-1, -2), params[1], [w.flip(-1, -2) for w in params[2]], params[3]
+    for t in (dev.x, dev.dy):
+        t[0, 0, H // 3, W // 2], t[0, 0, H // 3 + 1, W // 2 + 3], t[B - 1, C - 1, H - 1, W - 1] = inf, -inf, -inf
+    dx = binding.backward_data(dev.dy, dev.bw, dev.bs, dev.lw, dev.ls)
+    infinite = 0
+    for got, want in ((dev.forward(), plain_forward(f64(dev.x), *params)), (dx, plain_forward(f64(dev.dy), *rotated))):
+        got, bad = f64(got), ~torch.isfinite(want)
+        assert torch.equal(~torch.isfinite(got), bad)
+        assert torch.equal(torch.nan_to_num(got, 0, 1, -1)[bad], torch.nan_to_num(want, 0, 1, -1)[bad])
+        assert rel_err(got[~bad].numpy(), want[~bad].numpy()) < TOL[dtype]
+        infinite += int(torch.isinf(want).sum())
+    assert infinite > 0
