@@ -251,51 +251,88 @@ DEV double block_sum(const ST* __restrict__ plane, int H, int W, int l, int q, i
     const int half = 1 << (l - 1);
     double sum = 0.0;
 #pragma unroll 1
-    for (int y = j << l; y < min((j + 1) << l, H); ++y)
+    for (int y = j << l; y < min((j + 1) << l, H); y += 2)
 #pragma unroll 1
-        for (int x = i << l; x < min((i + 1) << l, W); ++x) {
-            const bool neg = ((q & 1) && (y & half)) != ((q >> 1) && (x & half));
-            const double v = to_f32(plane[(long)y * W + x]);
-            sum += neg ? -v : v;
+        for (int x = i << l; x < min((i + 1) << l, W); x += 2) {
+            double v[2][2];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int yy = y + (e >> 1), xx = x + (e & 1);
+                const bool neg = ((q & 1) && (yy & half)) != ((q >> 1) && (xx & half));
+                const double f = to_f32(plane[(long)min(yy, H - 1) * W + min(xx, W - 1)]);
+                v[e >> 1][e & 1] = yy < H && xx < W ? (neg ? -f : f) : 0.0;
+            }
+            sum += (v[0][0] + v[0][1]) + (v[1][0] + v[1][1]);
         }
     return sum;
 }
 
-// One kernel-gradient sum of a workgroup in plain arithmetic, over the pixels
-// [ya, ye) x [xa, xe) of nplanes planes: tap (pr, t) of the base kernel (l = 0)
-// or of band q of level l. The matrix products multiply the positions of a tile
-// outside the plane, and every phase of a band, by themselves: an infinity or
-// NaN in x or dy then reaches taps that do not pair with it, and the band's
-// infinities cancel to NaN. A sum that came out non-finite is therefore formed
-// again here. As in the vector kernels, dy meets the zeros around x (but on
-// planes of at most 8 x 8, whose vector kernel skips them). Cold: a thread walks
-// every plane, until its sum is NaN.
+// Whether [p, p + n) holds an infinity or NaN, for a whole wavefront.
+template <typename ST>
+DEV bool any_nonfinite(const ST* __restrict__ p, long n, int lane)
+{
+#pragma unroll 1
+    for (long i = 0; i < n; i += 64)
+        if (__ballot(i + lane < n && !(__builtin_fabsf(to_f32(p[min(i + lane, n - 1)])) < __builtin_inff()))) return true;
+    return false;
+}
+
+// One kernel-gradient sum per lane of a workgroup in plain arithmetic, over the
+// pixels [ya, ye) x [xa, xe) of nplanes planes: tap (pr, t) of the base kernel
+// (l = 0) or of band q of level l. The matrix products multiply the positions of
+// a tile outside the plane, and every phase of a band, by themselves: an
+// infinity or NaN in x or dy then reaches taps that do not pair with it, and the
+// band's infinities cancel to NaN. Sums that came out non-finite (`bad`) are
+// therefore formed again here, over the planes that hold such a value first:
+// the others only count where the sum is finite without them. As in the vector
+// kernels, dy meets the zeros around x (but on planes of at most 8 x 8, whose
+// vector kernel skips them). Called by whole wavefronts; cold.
 template <int K, typename ST>
 DEV float plain_sum(const ST* __restrict__ x, const ST* __restrict__ dy, int H, int W, int ya, int ye, int xa, int xe,
-                    int nplanes, long step, int l, int q, int pr, int t)
+                    int nplanes, long step, int l, int q, int pr, int t, bool bad, int lane)
 {
     constexpr int R = K / 2;
     const bool halo = H > kTinyMaxEdge || W > kTinyMaxEdge;
     const int h = (H + (1 << l) - 1) >> l, w = (W + (1 << l) - 1) >> l;
     const int j0 = ya >> l, j1 = (ye + (1 << l) - 1) >> l, i0 = xa >> l, i1 = (xe + (1 << l) - 1) >> l;
+    const int top = max(ya - 2 * R, 0), bottom = min(ye + 2 * R, H);  // rows of x that meet them (l <= 1 in regions)
     double sum = 0.0;
 #pragma unroll 1
-    for (int b = 0; b < nplanes; ++b, x += step, dy += step)
+    for (int pass = 0; pass < 2; ++pass) {
+        const bool open = bad && __builtin_fabs(sum) < __builtin_inf();
+        if (__ballot(open) == 0) break;
 #pragma unroll 1
-        for (int j = j0; j < j1; ++j) {
-            const int u = j + pr - R;
-            if (sum != sum || (!halo && (u < 0 || u >= h))) continue;
+        for (int b = 0; b < nplanes; ++b) {
+            const ST *xb = x + b * step, *db = dy + b * step;
+            const bool first = any_nonfinite<ST>(xb + (long)top * W, (long)(bottom - top) * W, lane) ||
+                               any_nonfinite<ST>(db + (long)ya * W, (long)(ye - ya) * W, lane);
+            if (first == (pass != 0) || !open) continue;
 #pragma unroll 1
-            for (int i = i0; i < i1; ++i) {
-                const int v = i + t - R;
-                const bool in = u >= 0 && u < h && v >= 0 && v < w;
-                if (!in && !halo) continue;
-                const double d = l == 0 ? (double)to_f32(dy[(long)j * W + i]) : block_sum<ST>(dy, H, W, l, q, j, i);
-                double m = 0.0;
-                if (in) m = l == 0 ? (double)to_f32(x[(long)u * W + v]) : block_sum<ST>(x, H, W, l, q, u, v);
-                sum += d * m;
+            for (int j = j0; j < j1; ++j) {
+                const int u = j + pr - R;
+                const bool row = u >= 0 && u < h;
+                if (sum != sum || (!row && !halo)) continue;
+                if (l == 0) {
+#pragma unroll 4
+                    for (int i = i0; i < i1; ++i) {
+                        const int v = i + t - R;
+                        const bool in = row && v >= 0 && v < w;
+                        const double d = to_f32(db[(long)j * W + i]), m = to_f32(xb[(long)min(max(u, 0), h - 1) * W + min(max(v, 0), w - 1)]);
+                        if (in || halo) sum += d * (in ? m : 0.0);
+                    }
+                } else {
+#pragma unroll 1
+                    for (int i = i0; i < i1; ++i) {
+                        const int v = i + t - R;
+                        const bool in = row && v >= 0 && v < w;
+                        if (!in && !halo) continue;
+                        const double m = in ? block_sum<ST>(xb, H, W, l, q, u, v) : 0.0;
+                        sum += block_sum<ST>(db, H, W, l, q, j, i) * m;
+                    }
+                }
             }
         }
+    }
     return (float)sum;
 }
 
@@ -418,18 +455,14 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
     const int NP = partial_floats_per_channel(K, a.L);
     float* dst = a.partial + ((long)ct * C + c) * NP;
     float* cm = reinterpret_cast<float*>(lds);
-    auto finite_or_plain = [&](float v, int l, int q, int pr, int t) {
-        if (__builtin_expect(__builtin_fabsf(v) < __builtin_inff(), 1)) return v;
-        const long first = ((long)b_begin * C + c) * HW;
-        return plain_sum<K, ST>(xs + first, ds + first, H, W, oy, ye, ox, xe, b_end - b_begin, (long)C * HW, l, q, pr, t);
-    };
     // Stage s's matrix gradient in cm -> its kernel gradients. Thread (q, tap):
     // band q of level s + 1; the last k k threads the base taps (stage 0).
     auto project = [&](int s) {
-        for (int e = tid; e < 5 * KK; e += kThreads) {
-            const int q = e / KK, tap = e - q * KK, pr = tap / K, t = tap - pr * K;
+        for (int e0 = 64 * wave; e0 < 5 * KK; e0 += kThreads) {
+            const int e = e0 + lane, q = e / KK, tap = e - q * KK, pr = tap / K, t = tap - pr * K;
+            const bool band = q < 4, base = q == 4 && s == 0;
             double sum = 0.0;  // (64 terms: their rounding would show)
-            if (q < 4) {
+            if (band) {
                 for (int m = 0; m < 16; ++m) {
                     const int pa = m >> 3, cb = m & 1, kc = 2 * (t + M / 2 - R + ((m & 7) >> 1));
                     for (int ap = 0; ap < 2; ++ap)
@@ -439,12 +472,22 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
                             sum += neg ? -v : v;
                         }
                 }
-                dst[KK + (4 * s + q) * KK + tap] =
-                    finite_or_plain(__builtin_ldexpf((float)sum, 4 * s), s + 1, q, pr, t);
-            } else if (s == 0) {
+            } else if (base) {
                 for (int m = 0; m < 16; ++m) sum += cm[entry(pr + R + (m >> 3), t + M - R + (m & 7), m)];
-                dst[tap] = a.skip_base ? 0.f : finite_or_plain((float)sum, 0, 0, pr, t);
+                if (a.skip_base) sum = 0.0;
             }
+            float g = band ? __builtin_ldexpf((float)sum, 4 * s) : (float)sum;
+            const bool bad = !(__builtin_fabsf(g) < __builtin_inff());
+            if (__builtin_expect(__ballot(bad) != 0, 0)) {
+                const long at = ((long)b_begin * C + c) * HW;
+                const float v = plain_sum<K, ST>(xs + at, ds + at, H, W, oy, ye, ox, xe, b_end - b_begin, (long)C * HW,
+                                                 band ? s + 1 : 0, q, pr, t, bad, lane);
+                g = bad ? v : g;
+            }
+            if (band)
+                dst[KK + (4 * s + q) * KK + tap] = g;
+            else if (base)
+                dst[tap] = g;
         }
     };
     const bool fine = !DEEP || wave < a.fine_waves;
