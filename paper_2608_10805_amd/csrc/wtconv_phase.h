@@ -229,6 +229,30 @@ DEV void raw_values(const RawBlock<ST>& b, float (&v)[4][4])
         }
 }
 
+// Signed sum (band q of the Haar butterfly) of the 2^l x 2^l block (j, i) of a
+// plane, zero-extended, at its true values.
+template <typename ST>
+DEV double block_sum(const ST* __restrict__ plane, int H, int W, int l, int q, int j, int i)
+{
+    const int half = 1 << (l - 1);
+    double sum = 0.0;
+#pragma unroll 1
+    for (int y = j << l; y < min((j + 1) << l, H); y += 2)
+#pragma unroll 1
+        for (int x = i << l; x < min((i + 1) << l, W); x += 2) {
+            double v[2][2];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int yy = y + (e >> 1), xx = x + (e & 1);
+                const bool neg = ((q & 1) && (yy & half)) != ((q >> 1) && (xx & half));
+                const double f = to_f32(plane[(long)min(yy, H - 1) * W + min(xx, W - 1)]);
+                v[e >> 1][e & 1] = yy < H && xx < W ? (neg ? -f : f) : 0.0;
+            }
+            sum += (v[0][0] + v[0][1]) + (v[1][0] + v[1][1]);
+        }
+    return sum;
+}
+
 // ----------------------------------------------------------------------------
 // weights
 // ----------------------------------------------------------------------------
@@ -236,23 +260,28 @@ DEV void raw_values(const RawBlock<ST>& b, float (&v)[4][4])
 // from: s0 W0 [k k], then per level the four phase combinations
 //   E[al][be] = 1/4 (LL +- LH +- HL +- HH), LH with the sign of al, HL of be,
 // HH of al ^ be, [2][2][k k] (taps reversed with rot). The products of two
-// float32 values and their sums are exact to float64.
+// float32 values and their sums are exact to float64. False if this thread met a
+// kernel that is not finite.
 template <int K>
 constexpr int staged_doubles(int L) { return (1 + 4 * L) * K * K; }
 template <int K>
-DEV void stage_kernels(const ParamPtrs& p, int c, int L, double* st, int tid)
+DEV bool stage_kernels(const ParamPtrs& p, int c, int L, double* st, int tid)
 {
     constexpr int KK = K * K;
     const bool rot = p.rot != 0;
+    bool finite = true;
     for (int e = tid; e < (1 + L) * KK; e += kThreads) {
         const int l = e / KK, t = e - l * KK, tap = rot ? KK - 1 - t : t;
         if (l == 0) {
             st[t] = (double)p.s0[c] * p.w0[(long)c * KK + tap];
+            finite = finite && __builtin_fabsf((float)st[t]) < __builtin_inff();
         } else {
             const float* w = p.lw[l - 1] + (long)4 * c * KK + tap;
             const float* s = p.ls[l - 1] + 4 * c;
             const double f0 = 0.25 * s[0] * w[0], f1 = 0.25 * s[1] * w[KK];
             const double f2 = 0.25 * s[2] * w[2 * KK], f3 = 0.25 * s[3] * w[3 * KK];
+            const double m = (__builtin_fabs(f0) + __builtin_fabs(f1)) + (__builtin_fabs(f2) + __builtin_fabs(f3));
+            finite = finite && (float)m < __builtin_inff();
             double* o = st + KK + 4 * (l - 1) * KK + t;
             o[0] = (f0 + f1) + (f2 + f3);
             o[KK] = (f0 + f1) - (f2 + f3);
@@ -260,6 +289,7 @@ DEV void stage_kernels(const ParamPtrs& p, int c, int L, double* st, int tid)
             o[3 * KK] = (f0 - f1) - (f2 - f3);
         }
     }
+    return finite;
 }
 
 // Coefficient of input column kc (counted from the tile's first column minus

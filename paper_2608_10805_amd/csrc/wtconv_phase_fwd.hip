@@ -30,7 +30,7 @@
 // 0 * inf is NaN: a non-finite input pixel would reach every output of the
 // tiles whose window holds it. Such pixels are zeroed and marked as they are
 // loaded, and the outputs that depend on one, and only they, become NaN. Where
-// one was an infinity, the workgroup goes over these outputs once more at its
+// one was an infinity (or a kernel of the channel is not finite), the workgroup goes over these outputs once more at its
 // end: an infinity remains where every term of it has the same sign.
 #include "wtconv_phase.h"
 
@@ -234,7 +234,8 @@ DEV void set_mark(uint16_t& m, uint16_t epoch)
 }
 DEV bool marked(uint16_t m, uint16_t epoch) { return (m >> 1) == epoch || m == 2 * (epoch + 1) + 1; }
 DEV int mark_cells(const PhaseArgs& a) { return a.L == 1 ? 4 * a.bx * a.by : a.bx * a.by; }
-// After the marks: whether any batch so far held an infinity.
+// After the marks: whether any batch so far held an infinity, or the channel has
+// a kernel that is not finite.
 DEV uint16_t& infinity_flag(const PhaseArgs& a, char* lds)
 {
     return reinterpret_cast<uint16_t*>(lds + a.mark_off)[a.PP * (1 + mark_cells(a))];
@@ -301,32 +302,39 @@ DEV int nonfinite_terms(const PhaseArgs& a, int c, float f, int py, int px, int 
     return cls;
 }
 
-// Whether every folded weight of channel c is finite.
-template <int K>
-DEV bool finite_weights(const PhaseArgs& a, int c, int lane)
+// Terms that non-finite folded weights of the channel add to output (y, x) of a
+// plane, classed the same way; the pixels around the plane are zeros.
+template <int K, typename ST>
+DEV int weight_terms(const PhaseArgs& a, int c, const ST* __restrict__ plane, int y, int x)
 {
-    constexpr int KK = K * K;
-    bool ok = true;
+    constexpr int R = K / 2, KK = K * K;
+    int cls = 0;
 #pragma unroll 1
-    for (int e = lane; e < (1 + 4 * a.L) * KK; e += 64) {
-        const int r = e / KK, t = e - r * KK, ch = 4 * c + ((r + 3) & 3);
-        const float g = r == 0 ? a.p.s0[c] * a.p.w0[(long)c * KK + t]
-                               : a.p.ls[(r - 1) / 4][ch] * a.p.lw[(r - 1) / 4][(long)ch * KK + t];
-        ok = ok && __builtin_fabsf(g) < __builtin_inff();
+    for (int e = a.skip_base ? KK : 0; e < (1 + 4 * a.L) * KK && cls != 3; ++e) {
+        const int r = e / KK, tap = e - r * KK, l = (r + 3) / 4, q = (r + 3) & 3;
+        const int t = a.p.rot ? KK - 1 - tap : tap, ch = 4 * c + q;
+        const float g = l == 0 ? a.p.s0[c] * a.p.w0[(long)c * KK + t] : a.p.ls[l - 1][ch] * a.p.lw[l - 1][(long)ch * KK + t];
+        if (__builtin_fabsf(g) < __builtin_inff()) continue;
+        const int j = (y >> l) + tap / K - R, i = (x >> l) + tap % K - R;
+        float v = 0.f;
+        if (j >= 0 && i >= 0 && (j << l) < a.H && (i << l) < a.W)
+            v = l == 0 ? to_f32(plane[(long)j * a.W + i]) : (float)block_sum<ST>(plane, a.H, a.W, l, q, j, i);
+        const bool neg = l > 0 && ((q & 1) && ((y >> (l - 1)) & 1)) != ((q >> 1) && ((x >> (l - 1)) & 1));
+        const float s = (neg ? -g : g) * v;
+        cls |= (s < 0.f ? 0 : 1) | (s > 0.f ? 0 : 2);
     }
-    return __ballot(!ok) == 0;
+    return cls;
 }
 
 // The wavefront's outputs that became NaN over the planes of its workgroup: an
-// infinity where all their non-finite terms, bias and carry included, have one
-// sign. The wavefront reads 64 pixels at a time. Everything is formed anew from
+// infinity where all their non-finite terms (of pixels, kernels, bias and carry)
+// have one sign. The wavefront reads 64 pixels at a time. Everything is formed anew from
 // the arguments, so that the kernel keeps nothing through its loop for this.
 template <int K, typename ST, bool RGN>
 DEV void restore_infinities(const PhaseArgs& a, int wave)
 {
     const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const int bid = (int)blockIdx.x - a.fin_blocks, c = bid % a.C;
-    if (!finite_weights<K>(a, c, lane)) return;
     const int ntiles = RGN ? a.rg_ntx * a.rg_nty : 1, chunk = (bid / a.C) / ntiles, tile = (bid / a.C) - chunk * ntiles;
     const int b_begin = chunk * a.nb, b_end = min(a.B, b_begin + a.nb);
     const int oy = RGN ? (tile / a.rg_ntx) * a.rg_th : 0, ox = RGN ? (tile % a.rg_ntx) * a.rg_tw : 0;
@@ -355,8 +363,9 @@ DEV void restore_infinities(const PhaseArgs& a, int wave)
             float extra = bias;
             if (RGN && a.carry)
                 extra += 0.5f * to_f32(reinterpret_cast<const ST*>(a.carry)[(pl * a.carry_H + (yy >> 1)) * a.carry_W + (xx >> 1)]);
-            if (!(extra < __builtin_inff())) pos |= 1u << e;
-            if (!(extra > -__builtin_inff())) neg |= 1u << e;
+            const int cls = weight_terms<K, ST>(a, c, ip, yy, xx);
+            if ((cls & 1) || !(extra < __builtin_inff())) pos |= 1u << e;
+            if ((cls & 2) || !(extra > -__builtin_inff())) neg |= 1u << e;
         }
 #pragma unroll 1
         for (long i0 = (long)y0 * a.W; i0 < (long)y1 * a.W && __ballot((open & ~(pos & neg)) != 0) != 0; i0 += 64) {
@@ -492,7 +501,7 @@ __global__ void __launch_bounds__(kThreads, (phase_waves<K, ST, NR>())) phase_ke
     // borrows the planes' area (the tap-by-tap path takes the weights anew).
     char* tab0 = lds + a.planes_off;
     double* st = reinterpret_cast<double*>(tab0 + 2 * SC::NW * tab_rows<K, true>() * kPhaseTabPitch);
-    stage_kernels<K>(a.p, c, a.L, st, tid);
+    const bool finite = stage_kernels<K>(a.p, c, a.L, st, tid);
     __syncthreads();
     float scale = 1.f, inv = 1.f;  // float16: powers of two that keep the weight pieces in range
     if constexpr (SC::F16) {
@@ -526,6 +535,7 @@ __global__ void __launch_bounds__(kThreads, (phase_waves<K, ST, NR>())) phase_ke
         for (int i = a.mark_off / 16 + tid; i < a.lds_bytes / 16; i += kThreads)
             lds4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         __syncthreads();
+        if (__builtin_expect(!finite, 0)) infinity_flag(a, lds) = 1;
     };
     // Roles: the first fine_waves wavefronts run stage 0, the others the deeper
     // stages lo .. hi. A wavefront of one stage keeps its weights in registers,

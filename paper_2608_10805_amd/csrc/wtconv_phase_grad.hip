@@ -243,30 +243,6 @@ DEV void put_acc(float* cm, const f32x4 (&acc)[2 * K], int lane, bool add)
     }
 }
 
-// Signed sum (band q of the Haar butterfly) of the 2^l x 2^l block (j, i) of a
-// plane, zero-extended, at its true values.
-template <typename ST>
-DEV double block_sum(const ST* __restrict__ plane, int H, int W, int l, int q, int j, int i)
-{
-    const int half = 1 << (l - 1);
-    double sum = 0.0;
-#pragma unroll 1
-    for (int y = j << l; y < min((j + 1) << l, H); y += 2)
-#pragma unroll 1
-        for (int x = i << l; x < min((i + 1) << l, W); x += 2) {
-            double v[2][2];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int yy = y + (e >> 1), xx = x + (e & 1);
-                const bool neg = ((q & 1) && (yy & half)) != ((q >> 1) && (xx & half));
-                const double f = to_f32(plane[(long)min(yy, H - 1) * W + min(xx, W - 1)]);
-                v[e >> 1][e & 1] = yy < H && xx < W ? (neg ? -f : f) : 0.0;
-            }
-            sum += (v[0][0] + v[0][1]) + (v[1][0] + v[1][1]);
-        }
-    return sum;
-}
-
 // Whether [p, p + n) holds an infinity or NaN, for a whole wavefront.
 template <typename ST>
 DEV bool any_nonfinite(const ST* __restrict__ p, long n, int lane)

@@ -274,3 +274,24 @@ def test_infinities_keep_their_sign(B, C, H, W, k, L, dtype):
         assert rel_err(got[~bad].numpy(), want[~bad].numpy()) < TOL[dtype]
         infinite += int(torch.isinf(want).sum())
     assert infinite > 0
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", [(3, 3, 57, 55, 5, 1, "f32"), (2, 3, 56, 56, 5, 3, "bf16"),
+                                               (3, 3, 56, 56, 3, 2, "f16"), (2, 3, 130, 128, 5, 1, "bf16")])
+@pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan")])
+def test_non_finite_kernels(B, C, H, W, k, L, dtype, value):
+    """One non-finite tap of the base kernel and of a level's band make their
+    channels what the sums have, and leave the other one as it is."""
+    inp, dev = setup(B, C, H, W, k, L, dtype, seed=4)
+    want = dev.forward()
+    dev.bw[0, 1, 2] = value
+    dev.lw[L - 1][4 + 2, 0, 0] = value
+    got = dev.forward()
+    assert torch.equal(got[:, 2], want[:, 2])
+    inside = torch.zeros(B, H, W, dtype=torch.bool, device=got.device)
+    R = k // 2
+    inside[:, max(R - 1, 0):, :W - max(2 - R, 0)] = True  # outputs whose tap (1, 2) meets a pixel
+    x = torch.nn.functional.pad(dev.x[:, 0].float(), [R] * 4)[:, 1:1 + H, 2:2 + W]
+    ref = torch.where(inside, x * value, torch.full_like(x, float("nan")))
+    assert torch.equal(torch.nan_to_num(got[:, 0].float(), 0, 1, -1), torch.nan_to_num(ref, 0, 1, -1))
+    assert not bool(torch.isfinite(got[:, 1]).any())
