@@ -303,27 +303,52 @@ DEV int nonfinite_terms(const PhaseArgs& a, int c, float f, int py, int px, int 
 }
 
 // Terms that non-finite folded weights of the channel add to output (y, x) of a
-// plane, classed the same way; the pixels around the plane are zeros.
+// plane, classed the same way; the pixels around the plane are zeros. On planes
+// of at most 8 x 8, whose vector kernel skips those, `rest` is the sum of the
+// other terms: the output, if there is none.
 template <int K, typename ST>
-DEV int weight_terms(const PhaseArgs& a, int c, const ST* __restrict__ plane, int y, int x)
+DEV int weight_terms(const PhaseArgs& a, int c, const ST* __restrict__ plane, int y, int x, float& rest)
 {
     constexpr int R = K / 2, KK = K * K;
+    const bool skip = a.H <= kTinyMaxEdge && a.W <= kTinyMaxEdge;
     int cls = 0;
 #pragma unroll 1
     for (int e = a.skip_base ? KK : 0; e < (1 + 4 * a.L) * KK && cls != 3; ++e) {
         const int r = e / KK, tap = e - r * KK, l = (r + 3) / 4, q = (r + 3) & 3;
         const int t = a.p.rot ? KK - 1 - tap : tap, ch = 4 * c + q;
         const float g = l == 0 ? a.p.s0[c] * a.p.w0[(long)c * KK + t] : a.p.ls[l - 1][ch] * a.p.lw[l - 1][(long)ch * KK + t];
-        if (__builtin_fabsf(g) < __builtin_inff()) continue;
+        const bool finite = __builtin_fabsf(g) < __builtin_inff();
+        if (finite && !skip) continue;
         const int j = (y >> l) + tap / K - R, i = (x >> l) + tap % K - R;
+        const bool in = j >= 0 && i >= 0 && (j << l) < a.H && (i << l) < a.W;
+        if (!in && skip) continue;
         float v = 0.f;
-        if (j >= 0 && i >= 0 && (j << l) < a.H && (i << l) < a.W)
-            v = l == 0 ? to_f32(plane[(long)j * a.W + i]) : (float)block_sum<ST>(plane, a.H, a.W, l, q, j, i);
+        if (in) v = l == 0 ? to_f32(plane[(long)j * a.W + i]) : (float)block_sum<ST>(plane, a.H, a.W, l, q, j, i);
         const bool neg = l > 0 && ((q & 1) && ((y >> (l - 1)) & 1)) != ((q >> 1) && ((x >> (l - 1)) & 1));
         const float s = (neg ? -g : g) * v;
+        if (finite) {
+            rest += __builtin_ldexpf(s, -2 * l);
+            continue;
+        }
         cls |= (s < 0.f ? 0 : 1) | (s > 0.f ? 0 : 2);
     }
     return cls;
+}
+
+// Whether every folded weight of channel c is finite.
+template <int K>
+DEV bool finite_weights(const PhaseArgs& a, int c, int lane)
+{
+    constexpr int KK = K * K;
+    bool ok = true;
+#pragma unroll 1
+    for (int e = lane; e < (1 + 4 * a.L) * KK; e += 64) {
+        const int r = e / KK, t = e - r * KK, ch = 4 * c + ((r + 3) & 3);
+        const float g = r == 0 ? a.p.s0[c] * a.p.w0[(long)c * KK + t]
+                               : a.p.ls[(r - 1) / 4][ch] * a.p.lw[(r - 1) / 4][(long)ch * KK + t];
+        ok = ok && __builtin_fabsf(g) < __builtin_inff();
+    }
+    return __ballot(!ok) == 0;
 }
 
 // The wavefront's outputs that became NaN over the planes of its workgroup: an
@@ -348,6 +373,7 @@ DEV void restore_infinities(const PhaseArgs& a, int wave)
     const float bias = (!a.skip_base && a.p.b0) ? a.p.s0[c] * a.p.b0[c] : 0.f;
     const long HW = (long)a.H * a.W;
     const int L = a.L;
+    const bool finite = finite_weights<K>(a, c, lane);
 #pragma unroll 1
     for (int b = b_begin; b < b_end; ++b) {
         const long pl = (long)b * a.C + c;
@@ -363,7 +389,11 @@ DEV void restore_infinities(const PhaseArgs& a, int wave)
             float extra = bias;
             if (RGN && a.carry)
                 extra += 0.5f * to_f32(reinterpret_cast<const ST*>(a.carry)[(pl * a.carry_H + (yy >> 1)) * a.carry_W + (xx >> 1)]);
-            const int cls = weight_terms<K, ST>(a, c, ip, yy, xx);
+            int cls = 0;
+            if (!finite) {
+                cls = weight_terms<K, ST>(a, c, ip, yy, xx, extra);
+                if (cls == 0 && __builtin_fabsf(extra) < __builtin_inff()) op[(long)yy * a.W + xx] = from_f32<ST>(extra);
+            }
             if ((cls & 1) || !(extra < __builtin_inff())) pos |= 1u << e;
             if ((cls & 2) || !(extra > -__builtin_inff())) neg |= 1u << e;
         }
