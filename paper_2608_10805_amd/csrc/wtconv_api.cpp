@@ -1291,7 +1291,7 @@ bool phase_layout(const wtconv_desc& d, wtc::PhaseArgs& a)
 {
     constexpr int M = wtc::kPhaseMargin;
     const int R = d.k / 2;
-    const int nx0 = d.dtype == WTCONV_F32 ? 3 : 1, nw0 = d.dtype == WTCONV_F16 ? 2 : 3;
+    const int nx0 = d.dtype == WTCONV_F32 ? 3 : 1, nw0 = 3;
     int tab = 0;
     long off = 0;
     for (int s = 0; s < std::max(a.L, 1); ++s) {
@@ -1345,7 +1345,7 @@ int phase_wgs(const wtconv_desc& d, const wtc::PhaseArgs& a, int rounds)
 // conversion, barriers and latencies.
 double phase_cycles(const wtconv_desc& d, const wtc::PhaseArgs& a, int rounds)
 {
-    const int np = d.dtype == WTCONV_F32 ? 6 : (d.dtype == WTCONV_BF16 ? 3 : 2);
+    const int np = d.dtype == WTCONV_F32 ? 6 : 3;
     const double fine = 16.0 * a.st[0].js * d.k * np + 40 * a.st[0].js;
     double coarse = 0, first = 0;
     for (int s = 1; s < a.L; ++s) {

@@ -5,9 +5,10 @@
 // Operands. The matrix cores take 16-bit operands and accumulate in float32.
 // A float32 value is split exactly into three bfloat16 pieces h + m + l (8
 // bits each), and a product keeps the six piece products down to 2^-16 of it;
-// the dropped ones are below 2^-24 together, about one float32 rounding. bfloat16 and float16 storage needs one piece for the
-// input itself (bfloat16 / float16 matrix instructions) and three / two for
-// the float32 weights; the block means of deeper stages are split in three.
+// the dropped ones are below 2^-24 together, about one float32 rounding.
+// bfloat16 and float16 storage needs one piece for the input itself (bfloat16 /
+// float16 matrix instructions) and three for the float32 weights; the block
+// means of deeper stages are split in three.
 #pragma once
 
 #include <type_traits>
@@ -41,7 +42,7 @@ struct Scheme<uint16_t> {
 };
 template <>
 struct Scheme<_Float16> {
-    static constexpr int NX = 1, NW = 2;
+    static constexpr int NX = 1, NW = 3;
     static constexpr bool F16 = true;
 };
 struct DeepScheme {  // stages >= 1, every storage type
@@ -323,7 +324,11 @@ constexpr int tab_rows() { return (BASE ? 8 : 4) * K; }
 // Fill the table of stage s from the staged kernels: piece i at i * tab_rows *
 // kPhaseTabPitch, row element u is the coefficient of input column kc = u - 6 (a
 // tile's column pair j reads from u = 6 - 2 j on). A thread fills two elements.
-// `scale` (a power of two) keeps float16 pieces in range.
+// float16 pieces: `scale` (a power of two) takes the channel's largest
+// coefficient to 2^14 or more, and the second and third piece are another 2^11
+// larger (kF16Step). Together they hold 33 bits, and weights down to 2^-26 of the
+// largest to float32's 24; below that the error is 2^-50 of the largest.
+constexpr float kF16Step = 2048.f;
 template <int K, bool BASE, bool F16>
 DEV void fill_table(const double* st, int s, bool base, char* tab, float scale, int tid)
 {
@@ -340,11 +345,15 @@ DEV void fill_table(const double* st, int s, bool base, char* tab, float scale, 
         const double v0 = phase_coeff<K>(st, s, BASE && base, pa, cb, pr, ap, u - 6);
         const double v1 = phase_coeff<K>(st, s, BASE && base, pa, cb, pr, ap, u - 5);
         if constexpr (F16) {
-            const float a = (float)(v0 * scale), b = (float)(v1 * scale);
-            const uint32_t h = pk_f16(a, b);
+            const double a = v0 * scale, b = v1 * scale;
+            const uint32_t h = pk_f16((float)a, (float)b);
             const f16x2 hv = __builtin_bit_cast(f16x2, h);
+            const double ra = (a - (double)hv.x) * kF16Step, rb = (b - (double)hv.y) * kF16Step;
+            const uint32_t m = pk_f16((float)ra, (float)rb);
+            const f16x2 mv = __builtin_bit_cast(f16x2, m);
             t32[e] = h;
-            t32[NR * P + e] = pk_f16((float)(v0 * scale - (double)(float)hv.x), (float)(v1 * scale - (double)(float)hv.y));
+            t32[NR * P + e] = m;
+            t32[2 * NR * P + e] = pk_f16((float)(ra - (double)mv.x), (float)(rb - (double)mv.y));
         } else {
             const uint32_t h = pk_bf16((float)v0, (float)v1);
             const float ra = (float)(v0 - (double)bf_lo(h)), rb = (float)(v1 - (double)bf_hi(h));
@@ -382,8 +391,8 @@ DEV void load_weights(const char* tab, int lane, u32x4 (&A)[K][3])
 // first 16 bytes in LDS (its window row ap, columns 8 seg .. 8 seg + 7) of
 // piece 0.
 // ----------------------------------------------------------------------------
-// With several pieces of x the products of the largest pieces come last, in a
-// second pass over the rows: the small products then round against small sums,
+// With several pieces of x, and in float16, the products of the largest pieces
+// come last, in a second pass over the rows: the small products then round against small sums,
 // and only k roundings of full size are left (measured against 64 bits at k =
 // 5, float32: 1.7e-7 with all products of a row together).
 template <int K, int JS, typename SC, int NA, bool BIG, bool SMALL, bool WHOLE>
@@ -395,8 +404,9 @@ DEV void run_pass(const char* lds, int off, int rp_bytes, int psz, const u32x4 (
     constexpr int R0 = WHOLE ? K / 2 : 0, N = WHOLE ? JS : JS + K - 1;
     // Rows in flight ahead of the products (no more: the scheduler would
     // otherwise hoist every read and spill). A row of the big pass alone is
-    // few products, so it reads further ahead.
-    constexpr int D = NX > 1 ? 2 : 4;
+    // few products, so it reads further ahead (k = 5: by one row less, for the
+    // registers; 256 x 256 B8 C128 L3 f16 forward 271 -> 243 us).
+    constexpr int D = NX > 1 ? 2 : (K > 3 ? 3 : 4);
     u32x4 b[D][NX];
     // (opaque: the runs of every length would share, and keep, their addresses)
     asm volatile("" : "+v"(off));
@@ -431,8 +441,12 @@ template <int K, int JS, typename SC, int NA, bool WHOLE = false>
 DEV void run_tiles(const char* lds, int off, int rp_bytes, int psz, const u32x4 (&A)[K][3], f32x4 (&acc)[NA])
 {
     static_assert(JS <= NA, "");
-    if constexpr (SC::NX > 1) {
+    if constexpr (SC::NX > 1 || SC::F16) {
         run_pass<K, JS, SC, NA, false, true, WHOLE>(lds, off, rp_bytes, psz, A, acc);
+        if constexpr (SC::F16) {  // (the small pieces are held kF16Step larger)
+#pragma unroll
+            for (int J = 0; J < JS; ++J) acc[J] *= 1.f / kF16Step;
+        }
         run_pass<K, JS, SC, NA, true, false, WHOLE>(lds, off, rp_bytes, psz, A, acc);
     } else {
         run_pass<K, JS, SC, NA, true, true, WHOLE>(lds, off, rp_bytes, psz, A, acc);

@@ -670,47 +670,58 @@ __global__ void __launch_bounds__(kThreads, (phase_waves<K, ST, NR>())) phase_ke
                 }
             }
         };
-        // region mode's carry: every row's values requested together (clamped:
-        // rows and columns past the grid feed pixels that are not stored)
-        float cr[MAXJS][2];
+        // region mode's carry: the values of G rows requested together, clamped
+        // (rows and columns past the grid feed pixels that are not stored). All
+        // rows' spill in float16 and float32 (256 x 256 B8 C128 L3 f16 forward 285
+        // us with all, 271 with four); in bfloat16 they are 1 % faster.
+        constexpr int G = SC::F16 || sizeof(ST) == 4 ? 4 : MAXJS;
         const bool carry = RGN && a.carry;
+        const ST* cp = nullptr;
+        int cx0 = 0, cx1 = 0;
         if constexpr (RGN) {
-            if (carry) {
-                const ST* cp = reinterpret_cast<const ST*>(a.carry) + ((long)b * C + c) * a.carry_H * a.carry_W;
-                const int cx0 = min((ox + x) >> 1, a.carry_W - 1), cx1 = min(cx0 + 1, a.carry_W - 1);
-#pragma unroll
-                for (int J = 0; J < MAXJS; ++J) {
-                    const int cy = min((oy >> 1) + j0 + J, a.carry_H - 1) * a.carry_W;
-                    cr[J][0] = to_f32(cp[cy + cx0]);
-                    cr[J][1] = to_f32(cp[cy + cx1]);
-                }
-            }
+            cp = reinterpret_cast<const ST*>(a.carry) + ((long)b * C + c) * a.carry_H * a.carry_W;
+            cx0 = min((ox + x) >> 1, a.carry_W - 1), cx1 = min(cx0 + 1, a.carry_W - 1);
         }
 #pragma unroll
-        for (int J = 0; J < MAXJS; ++J) {
-            if (J >= g.js) break;
-            if (J < nj) {
-                float o[4] = {acc[J][0], acc[J][1], acc[J][2], acc[J][3]};
-                float r0, r1;
-                coarse(j0 + J, r0, r1);
+        for (int J1 = 0; J1 < MAXJS; J1 += G) {
+            if (J1 >= g.js) break;
+            float cr[G][2];
+            if constexpr (RGN) {
                 if (carry) {
-                    r0 = __builtin_fmaf(0.5f, cr[J][0], r0);
-                    r1 = __builtin_fmaf(0.5f, cr[J][1], r1);
+#pragma unroll
+                    for (int J = 0; J < G; ++J) {
+                        const int cy = min((oy >> 1) + j0 + J1 + J, a.carry_H - 1) * a.carry_W;
+                        cr[J][0] = to_f32(cp[cy + cx0]);
+                        cr[J][1] = to_f32(cp[cy + cx1]);
+                    }
                 }
-                if constexpr (SC::F16) {
-                    o[0] = __builtin_fmaf(o[0], inv, r0);
-                    o[1] = __builtin_fmaf(o[1], inv, r0);
-                    o[2] = __builtin_fmaf(o[2], inv, r1);
-                    o[3] = __builtin_fmaf(o[3], inv, r1);
-                } else {
-                    o[0] += r0;
-                    o[1] += r0;
-                    o[2] += r1;
-                    o[3] += r1;
-                }
-                store4<ST>(op, off, x, xe, o);
             }
-            off += 2 * W;
+#pragma unroll
+            for (int J = J1; J < J1 + G && J < MAXJS; ++J) {
+                if (J >= g.js) break;
+                if (J < nj) {
+                    float o[4] = {acc[J][0], acc[J][1], acc[J][2], acc[J][3]};
+                    float r0, r1;
+                    coarse(j0 + J, r0, r1);
+                    if (carry) {
+                        r0 = __builtin_fmaf(0.5f, cr[J - J1][0], r0);
+                        r1 = __builtin_fmaf(0.5f, cr[J - J1][1], r1);
+                    }
+                    if constexpr (SC::F16) {
+                        o[0] = __builtin_fmaf(o[0], inv, r0);
+                        o[1] = __builtin_fmaf(o[1], inv, r0);
+                        o[2] = __builtin_fmaf(o[2], inv, r1);
+                        o[3] = __builtin_fmaf(o[3], inv, r1);
+                    } else {
+                        o[0] += r0;
+                        o[1] += r0;
+                        o[2] += r1;
+                        o[3] += r1;
+                    }
+                    store4<ST>(op, off, x, xe, o);
+                }
+                off += 2 * W;
+            }
         }
         if (__builtin_expect(marked(reinterpret_cast<const uint16_t*>(lds + a.mark_off)[sp], epoch), 0)) {
             // the plane holds non-finite pixels: NaN for the outputs that see one

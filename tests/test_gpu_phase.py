@@ -303,3 +303,21 @@ def test_non_finite_kernels(B, C, H, W, k, L, dtype, value):
     bad = ~torch.isfinite(ref)
     assert torch.equal(torch.isfinite(got[:, 0]), ~bad)
     assert torch.equal(torch.nan_to_num(got[:, 0].float(), 0, 1, -1)[bad], torch.nan_to_num(ref, 0, 1, -1)[bad])
+
+
+@pytest.mark.parametrize("H,W,k,L", [(56, 56, 5, 1), (57, 55, 3, 2), (130, 128, 5, 1)])
+def test_float16_kernels_keep_float32_accuracy(H, W, k, L):
+    """Taps 2^-34 of the channel's largest, each alone on a pixel: the outputs
+    are those of the float32 taps, to half a step of float16."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    C = 4
+    bw = (1 + torch.rand(C, k, k, generator=g, device="cuda")) * 2.0 ** -34
+    bw[:, k // 2, k // 2] = 1
+    one = torch.ones(C, device="cuda")
+    lw, ls = [torch.zeros(4 * C, k, k, device="cuda")] * L, [torch.ones(4 * C, device="cuda")] * L
+    x = torch.zeros(2, C, H, W, dtype=torch.float16, device="cuda")
+    x[:, :, H // 2, W // 2] = 60000
+    y = binding.forward(x, bw, one, lw, ls).double()
+    want = torch.nn.functional.conv2d(x.double(), bw.double()[:, None], padding=k // 2, groups=C)
+    want[:, :, H // 2, W // 2] = 60000
+    assert float((y - want).abs().max()) <= 2.0 ** -25 * 1.001
