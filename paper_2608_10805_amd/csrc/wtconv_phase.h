@@ -63,15 +63,18 @@ DEV uint32_t pk_f16(float a, float b)
 DEV float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 DEV float bf_hi(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
-// Two finite floats -> packed bfloat16 pieces h, m, l with v = h + m + l exactly.
-// h is cut off, not rounded: next to the largest float (a mask's lowest value)
-// rounding would make it infinite, and 0 * inf would reach outputs that do not
-// depend on the pixel.
+// Two finite floats -> packed bfloat16 pieces h, m, l with v = h + m + l, exactly
+// from 2^-110 on (below it l, then m, falls under bfloat16's smallest subnormal:
+// an error of up to 2^-134). h is rounded, which halves m and with it what the
+// dropped products leave out (2^-24.2 of a product at most over 2^24 random
+// pairs; with h cut off 2^-23.2), but never to infinity: next to the largest
+// float (a mask's lowest value) 0 * inf would reach outputs that do not depend on
+// the pixel.
 DEV void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l)
 {
-    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
-    const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
+    constexpr float top = 0x1.fep127f;  // the largest bfloat16
+    h = pk_bf16(__builtin_amdgcn_fmed3f(a, -top, top), __builtin_amdgcn_fmed3f(b, -top, top));
+    const float ra = a - bf_lo(h), rb = b - bf_hi(h);
     m = pk_bf16(ra, rb);
     l = pk_bf16(ra - bf_lo(m), rb - bf_hi(m));
 }
@@ -425,7 +428,7 @@ DEV void run_pass(const char* lds, int off, int rp_bytes, int psz, const u32x4 (
         for (int i = NX - 1; i >= 0; --i)
 #pragma unroll
             for (int j = SC::NW - 1; j >= 0; --j) {
-                if (i + j > 2) continue;  // below 2^-26 of the product
+                if (i + j > 2) continue;  // 2^-25 of the product or less each
                 if (i + j == 0 ? !BIG : !SMALL) continue;
 #pragma unroll
                 for (int J = 0; J < JS; ++J) {
