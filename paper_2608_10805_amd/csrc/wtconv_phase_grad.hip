@@ -149,15 +149,21 @@ DEV void corr_deep(const PhaseGradArgs& a, const char* lds, int s, int lane, f32
     corr_stage_js<K, 1, 3, 3, false, false>(a, lds, s, 0, 32, lane, acc, none);
 }
 
-// One block's pieces and block means on one side.
-template <typename ST, bool DEEP>
+// One block's pieces and block means on one side. With X (the x side) odd rows
+// are stored negated, and project() turns their sums back: the matrix
+// instructions round their sums down, and over the 64 entries that the LL band
+// adds up these errors met in one direction (56 x 56 B128 C96 L3 bf16, kernel
+// gradients of level 3 against 64 bits 4.1e-7, the vector pass 1.2e-7; B1024 C16
+// L1 f16, level 1 4.2e-7 and 3.6e-7). Now half of them point the other way.
+template <typename ST, bool DEEP, bool X>
 DEV void put_side(const PhaseSide& g, int L, int w2, char* plane, int y0, int x0, const RawBlock<ST>& raw)
 {
     const int M = g.margin;
     char* o = plane + g.off[0] + 2 * ((y0 + M) * g.pitch[0] + x0 + M);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-        *reinterpret_cast<uint2*>(o + 2 * r * g.pitch[0]) = make_uint2(raw.w[r][0], raw.w[r][1]);
+        *reinterpret_cast<uint2*>(o + 2 * r * g.pitch[0]) =
+            X && r % 2 ? make_uint2(raw.w[r][0] ^ 0x80008000u, raw.w[r][1] ^ 0x80008000u) : make_uint2(raw.w[r][0], raw.w[r][1]);
     if constexpr (!DEEP) return;
     float v[4][4];
     raw_values<ST>(raw, v);
@@ -168,7 +174,8 @@ DEV void put_side(const PhaseSide& g, int L, int w2, char* plane, int y0, int x0
         for (int j = 0; j < 2; ++j)
             s1[i][j] = mean4(v[2 * i][2 * j], v[2 * i][2 * j + 1], v[2 * i + 1][2 * j], v[2 * i + 1][2 * j + 1]);
         uint32_t h, m, l;
-        split2(s1[i][0], s1[i][1], h, m, l);
+        const bool neg = X && i == 1;
+        split2(neg ? -s1[i][0] : s1[i][0], neg ? -s1[i][1] : s1[i][1], h, m, l);
         char* q = plane + g.off[1] + 2 * (((y0 >> 1) + i + M) * g.pitch[1] + (x0 >> 1) + M);
         *reinterpret_cast<uint32_t*>(q) = h;
         *reinterpret_cast<uint32_t*>(q + g.psz[1]) = m;
@@ -177,7 +184,7 @@ DEV void put_side(const PhaseSide& g, int L, int w2, char* plane, int y0, int x0
     if (L < 3) return;
     const float s2 = mean4(s1[0][0], s1[0][1], s1[1][0], s1[1][1]);
     uint32_t h, m, l;
-    split2(s2, 0.f, h, m, l);
+    split2(X && (y0 & 4) ? -s2 : s2, 0.f, h, m, l);
     uint16_t* q = reinterpret_cast<uint16_t*>(plane + g.off[2]) + ((y0 >> 2) + M) * g.pitch[2] + (x0 >> 2) + M;
     q[0] = (uint16_t)h;
     q[g.psz[2] / 2] = (uint16_t)m;
@@ -186,6 +193,7 @@ DEV void put_side(const PhaseSide& g, int L, int w2, char* plane, int y0, int x0
 }
 
 // The means of stage s >= 3 on one side, from stage s - 1's, by one wavefront.
+template <bool X>
 DEV void deepen_side(const PhaseGradArgs& a, const PhaseSide& g, char* lds, int s, int lane)
 {
     asm volatile("" : "+v"(lane));
@@ -202,7 +210,7 @@ DEV void deepen_side(const PhaseGradArgs& a, const PhaseSide& g, char* lds, int 
         const float v = mean4(v00, v01, v10, v11);
         if (s + 1 < a.L) reinterpret_cast<float*>(plane + g.mf[s])[j * w + i] = v;
         uint32_t hh, m, l;
-        split2(v, 0.f, hh, m, l);
+        split2(X && (j & 1) ? -v : v, 0.f, hh, m, l);
         uint16_t* o = reinterpret_cast<uint16_t*>(plane + g.off[s]) + (j + g.margin) * g.pitch[s] + i + g.margin;
         o[0] = (uint16_t)hh;
         o[g.psz[s] / 2] = (uint16_t)m;
@@ -392,7 +400,7 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
                 const bool have = b0 + xp[i] < b_end;
                 if (have) {
                     if (ragged) mask_raw<ST>(H, W, oy + y0, ox + x0, edge, vx[i]);
-                    put_side<ST, DEEP>(a.sx, a.L, a.w[ND > 1 ? 2 : 0], plane, y0, x0, vx[i]);
+                    put_side<ST, DEEP, true>(a.sx, a.L, a.w[ND > 1 ? 2 : 0], plane, y0, x0, vx[i]);
                     if constexpr (RGN)
                         if (a.cx && y0 >= 0 && y0 < a.rg_T && x0 >= 0 && x0 < a.rg_T)
                             put_carrier<ST>(reinterpret_cast<ST*>(a.cx) + ((long)(b0 + xp[i]) * C + c) * a.cH * a.cW,
@@ -407,7 +415,7 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
 #pragma unroll
                             for (int j = 0; j < RawBlock<ST>::NW; ++j) vd[i].w[r][j] = 0;
                     }
-                    put_side<ST, DEEP>(a.sd, a.L, a.w[ND > 1 ? 2 : 0], plane, y0, x0, vd[i]);
+                    put_side<ST, DEEP, false>(a.sd, a.L, a.w[ND > 1 ? 2 : 0], plane, y0, x0, vd[i]);
                 }
             }
             if constexpr (RGN) {
@@ -415,7 +423,7 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
                 asm volatile("" : "+v"(v0), "+v"(u0));
                 if (dp[i] < 1) {
                     mask_raw<ST>(H, W, oy + v0, ox + u0, edge, vd[i]);
-                    put_side<ST, false>(a.sd, 1, 0, lds, v0, u0, vd[i]);
+                    put_side<ST, false, false>(a.sd, 1, 0, lds, v0, u0, vd[i]);
                     if (a.cdy)
                         put_carrier<ST>(reinterpret_cast<ST*>(a.cdy) + ((long)b0 * C + c) * a.cH * a.cW, a.cH, a.cW,
                                         oy + v0, ox + u0, vd[i]);
@@ -444,12 +452,15 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
                     for (int ap = 0; ap < 2; ++ap)
                         for (int be = 0; be < 2; ++be) {
                             const float v = cm[entry(2 * pr + ap, kc + be, m)];
-                            const int neg = ((q & 1) & (pa ^ ap)) ^ ((q >> 1) & (cb ^ be));
+                            const int neg = ((q & 1) & (pa ^ ap)) ^ ((q >> 1) & (cb ^ be)) ^ ap;
                             sum += neg ? -v : v;
                         }
                 }
             } else if (base) {
-                for (int m = 0; m < 16; ++m) sum += cm[entry(pr + R + (m >> 3), t + M - R + (m & 7), m)];
+                for (int m = 0; m < 16; ++m) {
+                    const float v = cm[entry(pr + R + (m >> 3), t + M - R + (m & 7), m)];
+                    sum += (pr + R + (m >> 3)) & 1 ? -v : v;
+                }
                 if (a.skip_base) sum = 0.0;
             }
             float g = band ? __builtin_ldexpf((float)sum, 4 * s) : (float)sum;
@@ -531,8 +542,8 @@ __global__ void __launch_bounds__(kThreads, (grad_waves<NR, ND>())) phase_grad_k
                 for (int i = 0; i < NS; ++i)
                     if (3 + i < a.L) {
                         asm volatile("" ::: "memory");
-                        deepen_side(a, a.sx, lds, 3 + i, lane);
-                        deepen_side(a, a.sd, lds, 3 + i, lane);
+                        deepen_side<true>(a, a.sx, lds, 3 + i, lane);
+                        deepen_side<false>(a, a.sd, lds, 3 + i, lane);
                         asm volatile("" ::: "memory");
                         corr_deep<K>(a, lds, 3 + i, lane, acc[i]);
                     }
