@@ -327,9 +327,9 @@ def test_float16_kernels_keep_float32_accuracy(H, W, k, L):
                                                (96, 8, 28, 28, 3, 3, "f16")])
 def test_kernel_gradients_of_deep_levels_have_no_bias(B, C, H, W, k, L, dtype):
     """Rounding errors of one direction would add up over the planes: every
-    level's gradient to 2e-7 of its norm (independent errors of float32 sums
-    measure 1e-7 here, and 3e-7 to 5e-7 with the bias), its mean error to 5e-8
-    of its largest band."""
+    level's gradient to 1.5e-7 of its norm (independent errors of float32 sums
+    measure 5e-8 to 8e-8 here, and 3e-7 to 5e-7 with the bias), its mean error
+    over a band to half of that."""
     inp, dev = setup(B, C, H, W, k, L, dtype, seed=6)
     out = dev.backward()
     tap_sums.tiny = False
@@ -338,6 +338,6 @@ def test_kernel_gradients_of_deep_levels_have_no_bias(B, C, H, W, k, L, dtype):
         x, dy = haar_bands(x), haar_bands(dy)
         want = tap_sums(dy, x, k).cpu()
         got = (out[3][l].double() / dev.ls[l].double().view(-1, 1, 1)).view(C, 4, k, k).cpu()
-        assert float((got - want).norm() / want.norm()) < 2e-7
-        assert float((got - want).mean((0, 2, 3)).abs().max() / want.pow(2).mean().sqrt()) < 5e-8
+        assert float((got - want).norm() / want.norm()) < 1.5e-7
+        assert float((got - want).mean((0, 2, 3)).abs().max() / want.pow(2).mean().sqrt()) < 7.5e-8
         x, dy = x[:, :, 0], dy[:, :, 0]
