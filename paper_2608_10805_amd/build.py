@@ -17,7 +17,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libwtconv.so")
 SOURCES = ["wtconv_api.cpp", "wtconv_noalloc.cpp", "wtconv_fwd.hip", "wtconv_mixed.hip", "wtconv_bwd.hip",
-           "wtconv_bwd9.hip", "wtconv_phase_fwd.hip", "wtconv_phase_grad.hip", "wtconv_grad.hip", "wtconv_kernels.hip", "wtconv_tiny.hip"]
+           "wtconv_bwd9.hip", "wtconv_phase_fwd.hip", "wtconv_phase_grad.hip", "wtconv_grad.hip",
+           "wtconv_kernels.hip", "wtconv_tiny.hip"]
 # measurement helper used only by the benchmark (sustained VALU rate)
 PROBE_LIB = os.path.join(HERE, "libvalu_probe.so")
 PROBE_SOURCES = ["valu_probe.hip"]
@@ -58,14 +59,33 @@ def _compile(sources, lib, extra, verbose):
     os.replace(lib + ".tmp", lib)
 
 
+def _torch_toolchain():
+    """(g++, torch's folder), or None where one of them or torch's headers is
+    missing: the wrapper then runs from Python alone."""
+    import importlib.util
+    import shutil
+
+    gxx, spec = shutil.which("g++"), importlib.util.find_spec("torch")
+    t = os.path.dirname(spec.origin) if spec and spec.origin else ""
+    if not gxx or not os.path.exists(os.path.join(t, "include", "torch", "extension.h")):
+        return None
+    return gxx, t
+
+
 def _compile_torch(verbose):
     import sysconfig
 
+    found = _torch_toolchain()
+    if found is None:
+        print("no g++ or no torch headers: the autograd wrapper's native host path is left out", flush=True)
+        if os.path.exists(TORCH_LIB):  # (of other sources, perhaps)
+            os.remove(TORCH_LIB)
+        return
     import torch
-    t = os.path.dirname(torch.__file__)
+    gxx, t = found
     includes = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
                 os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    cmd = [gxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-DTORCH_EXTENSION_NAME=_wtconv_torch",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", INCLUDE]
     for d in includes:
@@ -80,7 +100,8 @@ def _compile_torch(verbose):
 
 def build(verbose: bool = False, extra=None) -> str:
     """Compile every HIP source (libwtconv.so and the benchmark's VALU probe) and
-    the autograd wrapper's native host path; return the path of libwtconv.so."""
+    the autograd wrapper's native host path (where g++ and torch's headers are
+    there); return the path of libwtconv.so."""
     _compile(SOURCES, LIB, extra, verbose)
     _compile_torch(verbose)
     _compile(PROBE_SOURCES, PROBE_LIB, extra, verbose)
