@@ -351,12 +351,12 @@ DEV void fill_table(const double* st, int s, bool base, char* tab, float scale, 
             const double a = v0 * scale, b = v1 * scale;
             const uint32_t h = pk_f16((float)a, (float)b);
             const f16x2 hv = __builtin_bit_cast(f16x2, h);
-            const double ra = (a - (double)hv.x) * kF16Step, rb = (b - (double)hv.y) * kF16Step;
-            const uint32_t m = pk_f16((float)ra, (float)rb);
+            const float ra = (float)(a - (double)hv.x) * kF16Step, rb = (float)(b - (double)hv.y) * kF16Step;
+            const uint32_t m = pk_f16(ra, rb);
             const f16x2 mv = __builtin_bit_cast(f16x2, m);
             t32[e] = h;
             t32[NR * P + e] = m;
-            t32[2 * NR * P + e] = pk_f16((float)(ra - (double)mv.x), (float)(rb - (double)mv.y));
+            t32[2 * NR * P + e] = pk_f16(ra - (float)mv.x, rb - (float)mv.y);
         } else {
             const uint32_t h = pk_bf16((float)v0, (float)v1);
             const float ra = (float)(v0 - (double)bf_lo(h)), rb = (float)(v1 - (double)bf_hi(h));
