@@ -1171,17 +1171,40 @@ bool phase_grad_offered(const wtconv_desc& d)
            (!use_tiny(d) || d.L == 1);  // tiny planes: L = 1 alone (training step 7 x 7 B128 C768 71 -> 58 us, L2 79 -> 96)
 }
 
+// Planes of at most 8 x 8 have the one-plane-per-lane kernel. At L = 1 in 16
+// bits the polyphase forward is faster on rows of whole vectors (8 x 8 B128 C768
+// 18.5 -> 13.7 us) and where 64 planes per wavefront leave the chip idle: 7 x 7,
+// 6 x 6 and 5 x 5, 24576 planes 0.66-0.93 of its time, 49152 0.80-0.89 at k = 5
+// and 1.02-1.13 at k = 3, 98304 0.92-1.30.
+constexpr long kPhaseTinyPlanes = 32768;
+
+bool phase_tiny_pays(const wtconv_desc& d)
+{
+    return d.dtype != WTCONV_F32 && d.L == 1 && (d.W % 4 == 0 || (long)d.B * d.C < kPhaseTinyPlanes);
+}
+
 // Where the polyphase gradient pass is the faster one. Measured on MI355X,
-// training step with it / with the vector gradient pass (bf16, k = 5 and 3):
-// 0.45 (63 x 95 L1) to 0.95, most 0.6-0.85; 14 x 14 L5 B128 C384, where the
-// one-plane-per-lane coarse kernel has enough planes, 1.13; 56 x 56 L4 and L5
-// with 1536 planes (four deeper stages hold it to two workgroups per CU) 1.05.
+// training step with it / with the vector gradient pass (16-bit, k = 5 and 3):
+// 0.45 (63 x 95 L1) to 0.95, most 0.6-0.85. Not so at
+//  - L = 5 and k = 5 on planes up to 16 x 16 with enough planes for the
+//    one-plane-per-lane coarse kernel (14 x 14, 10 x 10: 12288 planes 0.92, 0.93,
+//    24576 0.98, 1.03, 36864 1.13, 1.14; k = 3 0.75-0.90 at all of them);
+//  - L = 4 and 5 with few planes (four deeper stages hold it to two workgroups
+//    per CU): 56 x 56 and 52 x 52 with 1536 planes 0.95-1.05, 64 x 64 with 3072
+//    0.87-0.99, 56 x 56 with 3840 0.88-0.96; planes up to 48 x 48 gain with any;
+//  - L = 1 on planes up to 8 x 8 (a backward of one launch, dx included) where
+//    that launch is one round of workgroups and dx would not be polyphase: 7 x 7,
+//    6 x 6 and 5 x 5 B64 C768 1.08-1.14; two rounds, B128, 0.82-0.91; dx
+//    polyphase, B32, 0.88-1.00.
+constexpr long kPhaseGradDeepPlanes = 3072, kPhaseGradSmallL5Planes = 24576;
+
 bool phase_grad_pays(const wtconv_desc& d)
 {
     const int edge = std::max(d.H, d.W);
     const long planes = (long)d.B * d.C;
-    if (d.L == 5 && edge <= 16 && planes >= kSplitMinPlanes) return false;
-    return d.L <= 3 || edge <= 48 || planes >= 4096;
+    if (use_tiny(d)) return phase_tiny_pays(d) || (long)cdiv(d.C, 4) * tiny_groups(d) > 256;
+    if (d.L == 5 && d.k == 5 && edge <= 16 && planes >= kPhaseGradSmallL5Planes) return false;
+    return d.L <= 3 || edge <= 48 || planes >= kPhaseGradDeepPlanes;
 }
 
 GradExec choose_grad_uncached(const wtconv_desc& d);
@@ -1549,13 +1572,7 @@ PhaseExec choose_phase(const wtconv_desc& d, int skip_base, bool region = false)
     // sub-problems 250; backward 382, 443).
     if (skip_base && d.dtype == WTCONV_F32) return none;
     if (region && d.dtype == WTCONV_F32 && !phase_f32_tiles_pay(d)) return none;
-    // Planes of at most 8 x 8 have the one-plane-per-lane kernel. At L = 1 in 16
-    // bits the polyphase one is faster on rows of whole vectors (8 x 8 B128 C768
-    // 18.5 -> 13.7 us) and where 64 planes per wavefront leave the chip idle
-    // (7 x 7 B32 C256 12.9 -> 8.7; B128 C768 18.9 -> 19.8 stays).
-    if (use_tiny(d) &&
-        (d.dtype == WTCONV_F32 || d.L > 1 || (d.W % 4 != 0 && (long)d.B * d.C >= kSplitMinPlanes)))
-        return none;
+    if (use_tiny(d) && !phase_tiny_pays(d)) return none;
     static PlanCache<PhaseExec> cache;
     return cache.get(d, region ? 1 : 0, [&] {
         PhaseExec e;

@@ -170,6 +170,39 @@ def test_polyphase_plans_hold_their_invariants(phase_check):
     assert all(sum(o.split()[i] == "1" for o in out) > 800 for i in (1, 2, 3))
 
 
+@pytest.fixture(scope="module")
+def phase_routes(tmp_path_factory):
+    """(B, C, H, W, k, L, dtype) tuples -> [(forward route, PP, batches, last,
+    gradient route, PP, batches, last)], see tests/planner/phase_routes.cpp."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("needs g++")
+    exe = str(tmp_path_factory.mktemp("routes") / "phase_routes")
+    subprocess.run([gxx, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "c++",
+                    os.path.join(ROOT, "tests", "planner", "phase_routes.cpp"), "-o", exe,
+                    "-L", "/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True,
+                   capture_output=True)
+
+    def run(specs):
+        lines = [" ".join(map(str, (*s[:6], ("f32", "bf16", "f16").index(s[6])))) for s in specs]
+        out = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True,
+                             timeout=60).stdout.strip().split("\n")
+        return [tuple(map(int, line.split())) for line in out]
+
+    return run
+
+
+# on both sides of every line of the gradient rule; the times are at the rule
+@pytest.mark.parametrize("spec,phase", [
+    ((64, 768, 7, 7, 5, 1, "bf16"), 0), ((128, 768, 7, 7, 5, 1, "bf16"), 1), ((32, 768, 7, 7, 3, 1, "f16"), 1),
+    ((64, 768, 8, 8, 5, 1, "f16"), 1), ((64, 384, 10, 10, 5, 5, "bf16"), 0), ((32, 384, 14, 14, 5, 5, "bf16"), 1),
+    ((128, 384, 14, 14, 3, 5, "f16"), 1), ((16, 96, 56, 56, 5, 4, "bf16"), 0), ((32, 96, 64, 64, 5, 4, "bf16"), 1),
+    ((16, 64, 48, 48, 5, 5, "f16"), 1), ((64, 96, 56, 56, 5, 3, "f32"), 0)])
+def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
+    assert phase_routes([spec])[0][4] == phase
+
+
 def test_odd_shape_block_rounds(planner):
     """63 x 95 planes have 384 4x4 blocks: the gradient pass takes them in
     two rounds over one resident plane."""
