@@ -1502,17 +1502,18 @@ bool make_phase_region_plan(const wtconv_desc& d, PhasePlan& out)
     return best >= 0;
 }
 
-// float32 region tiles with a carry: the polyphase tiles win where the vector
-// kernels' 56 x 56 tiles are mostly padding (polyphase / vector forward, k = 5
-// and 3: 120 x 120 0.94, 128 x 128 0.81-0.95, with dx 0.93-0.98) and lose where
-// these fit (112 x 112 1.02-1.06, 140 x 140 1.09, 160 x 160 1.03, 224 x 224
-// 1.04) or on planes up to 112 pixels (72 x 72 L3 1.29). Between them it depends on the batch (100 x 100 0.99 and dx 1.015, 150 x
-// 150 0.94-1.07, 256 x 256 0.98 and dx 1.05): the vector kernels stay.
+// float32 region tiles with a carry (the vector forward in tiles too): the
+// polyphase tiles win where the vector kernels' 56 x 56 tiles are mostly padding.
+// Padded area over the plane's, and polyphase / vector training step, k = 5 and
+// 3: 60 x 170 2.5, 0.86; 116 x 116 2.1, 0.89, 0.84; 116 x 170 1.9, 0.85; 128 x
+// 128 1.7, 0.86-0.89, 0.82-0.85; 169 x 169 1.8, 0.96, 0.92. Below it depends on
+// the card and the batch: 134 x 134 1.6, 0.92, 0.90; 140 x 140 1.4, 0.92 (1.09 on
+// another card); 150 x 150 1.25, 0.93 (0.94-1.07); 196 x 196 1.3, 1.00, 1.05;
+// 224 x 224 1.0, 0.97, 0.98 (1.04); 100 x 250 1.25, 1.09: the vector kernels stay.
 bool phase_f32_tiles_pay(const wtconv_desc& d)
 {
     const long tiled = 56L * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
-    const int edge = std::max(d.H, d.W);
-    return edge > 112 && edge <= 136 && 10 * tiled >= 17L * d.H * d.W;
+    return 10 * tiled >= 17L * d.H * d.W && choose(d, false).mode == Mode::Region;
 }
 
 // Where the polyphase forward is the faster one. Measured on MI355X against the

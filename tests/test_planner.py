@@ -203,6 +203,16 @@ def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
     assert phase_routes([spec])[0][4] == phase
 
 
+# on both sides of every line of the forward rule; the times are at the rule
+@pytest.mark.parametrize("spec,route", [
+    ((8, 64, 116, 116, 5, 2, "f32"), 2), ((8, 64, 128, 128, 3, 3, "f32"), 2), ((8, 64, 134, 134, 5, 2, "f32"), 0),
+    ((8, 64, 169, 169, 5, 3, "f32"), 2), ((8, 64, 170, 170, 3, 2, "f32"), 2), ((8, 64, 116, 170, 5, 2, "f32"), 2),
+    ((8, 64, 60, 170, 5, 3, "f32"), 2), ((16, 64, 224, 224, 5, 3, "f32"), 0), ((16, 64, 100, 100, 5, 2, "f32"), 0),
+    ((16, 96, 72, 72, 5, 4, "f32"), 0), ((16, 64, 224, 224, 5, 3, "bf16"), 2)])
+def test_where_the_forward_is_polyphase(phase_routes, spec, route):
+    assert phase_routes([spec])[0][0] == route
+
+
 def test_odd_shape_block_rounds(planner):
     """63 x 95 planes have 384 4x4 blocks: the gradient pass takes them in
     two rounds over one resident plane."""
