@@ -1516,47 +1516,87 @@ bool phase_f32_tiles_pay(const wtconv_desc& d)
     return 10 * tiled >= 17L * d.H * d.W && choose(d, false).mode == Mode::Region;
 }
 
+// Lane-cycles per plane of the two forwards as their planners model them,
+// polyphase over vector (whose general variant runs at 3/4 of the single-round
+// one); `busy`: how much of a CU's lanes the vector plan fills.
+double phase_model_ratio(const wtconv_desc& d, const wtc::PhaseArgs& a, int rounds, const Exec& ex, double& busy)
+{
+    const Plan& pl = ex.pl;
+    const int wgs = std::min(4, std::min(forward_wgs(d, pl.one_round != 0), lds_wgs(pl.lds_floats)));
+    const bool mixed = pl.mx.rounds > 0;
+    busy = tile_use(pl.g, pl.PP) * wgs / 4;
+    const double issue = 4 * (mixed ? issue_mixed(d, pl.PP, pl.mx) : issue_fused(d, pl.PP, pl.g, pl.merge_deep != 0));
+    return phase_cycles(d, a, rounds) / a.PP / phase_wgs(d, a, rounds) / issue * (mixed || pl.one_round ? 1.0 : 0.75);
+}
+
 // Where the polyphase forward is the faster one. Measured on MI355X against the
-// vector kernels (forward time, polyphase / vector; k = 5 and 3):
-//  - 16-bit storage, L <= 4: 0.30 (63 x 95 L1) to 0.99, most shapes 0.45-0.75;
-//    float32, L = 1:
-//    0.61 (128 x 128) to 0.98, training steps 0.82 to 1.02;
-//  - float32, L = 2 and 3, k = 5 (training steps): the matrix instructions take
-//    as long as the vector kernels' FMAs where these have their lanes full (56 x
-//    56 L2 1.007, L3 1.017 to 1.05 by card, as the gradient pass after it clocks
-//    lower; 64 x 64 1.02, 1.08; 40 x 40 L2 1.037; 32 x 32 L2 1.025), less where
-//    a quarter or more of the 4 x 4 blocks' lanes idle (48 x 48 0.90, 0.89; 63 x
-//    95 0.83, 0.88; 47 x 61 1.006, 0.98) and on the smallest planes (20 x 20 L2
-//    0.95, 14 x 14 L2 0.94); k = 3: 0.93-0.95, two rounds of blocks at L3 1.03;
+// vector kernels (polyphase / vector, k = 5 and 3):
+//  - float32, L = 1: forward 0.61 (63 x 95) to 1.01, training step 0.76 to 1.01;
+//    16-bit storage, L <= 4: forward 0.30 (63 x 95 L1) to 0.99, most 0.45-0.75;
+//  - few batches of planes for the workgroups that are resident at once do not
+//    make up for the weight tables, formed in float64, against a vector plan of
+//    one round. Training step by batches per such workgroup: float32 at L2-L3 0.1
+//    to 1.3 0.99-1.40 (48 x 48), 2.0 0.99-1.005, 8 0.89-0.96; 16 bits at L >= 4
+//    0.1 to 1.3 1.00-1.15 (56 x 56, 64 x 64, 28 x 28), 2.0 0.93-1.02, 4 0.85-0.95;
+//    float16 at L2-L3 0.5 (64 x 64) 1.02-1.05, 0.7 0.96-1.02, 1.3 0.98-0.99;
+//  - float32, L = 2 and 3: nothing is gained where fewer planes per CU are
+//    resident than in the vector plan, up to three (training step, 64 x 64 k3 L3
+//    1.16; 72 x 72 k3 L2 1.29, k5 L3 1.27; 50 x 70 k3 L3 1.09);
+//  - then at k = 5 the matrix instructions take as long as the vector kernels'
+//    FMAs where these have their lanes full (56 x 56 L2 0.95 to 1.007 by card, L3
+//    0.96 to 1.05; 64 x 64 L2 0.98 to 1.02; 40 x 40 L2 0.98 to 1.04), less where a
+//    quarter or more of the 4 x 4 blocks' lanes idle (48 x 48 0.90; 63 x 95 0.78,
+//    0.81; 47 x 61 0.95 to 1.006, 0.98) or three workgroups per CU with 30 % of
+//    their lanes idle (60 x 60 L2 0.87; 55 x 57 L3 0.91; 32 x 32 L3 0.90; 44 x 44
+//    0.95, 0.94), while the model gives it half of the vector kernels' time (28 x
+//    28 0.51 and 0.59: 0.99; 31 x 47 L3 0.61: 1.11), and on the smallest planes at
+//    L = 2 (20 x 20 0.97, 14 x 14 0.96);
+//  - at k = 3 where the model ratio is at most 1.4 (28 x 28 L3 1.26: 0.99; 24 x 24
+//    L2 1.33: 0.90; 35 x 90 L3 1.46: 1.08), 0.95 if the vector lanes are 75 % full
+//    (40 x 40 L2 0.91: 0.96; 32 x 32 L2 1.01 and L3 1.26: 1.01-1.04) and 0.9 at 80 %
+//    (55 x 57 L3 0.90: 0.99; 35 x 90 L2 0.91 and 50 x 70 L2 1.2: 1.03); at L3 with
+//    one round of blocks (two spill: 72 x 72 1.14);
 //  - float32, L >= 4: 0.84 to 1.8 (its deeper stages need six products per
 //    term and one wavefront runs them);
 //  - 16-bit, L = 5: 56 x 56 0.88, 28 x 28 0.75, 20 x 20 0.78, but 40 x 40 1.08
-//    and 14 x 14 at 49152 planes, where the split's one-plane-per-lane kernel
-//    has enough planes, 1.12;
+//    and, where the split's one-plane-per-lane kernel has enough planes, 14 x 14
+//    and 10 x 10 (training step, k = 5: 24576 planes 0.87, 0.81, 36864 1.10, 1.05);
 //  - L >= 2 on planes that go one to a batch and leave more than half the
 //    threads without a block (31 x 47): 1.02-1.4;
 //  - a plane too tall for one workgroup's columns runs in region tiles with a
 //    carrier pass; where the vector kernels hold it whole they are faster at
 //    L >= 2 (84 x 84 1.4-1.9); float32 at L >= 2: phase_f32_tiles_pay().
+constexpr long kPhaseSmallL5Planes = 32768;
+
 bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
 {
     if (e.kind == PhaseExec::None) return false;
     const int edge = std::max(d.H, d.W);
+    const Exec ex = choose(d, false);
     if (e.kind == PhaseExec::Region)
-        return choose(d, false).mode == Mode::Region &&
-               (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d));
+        return ex.mode == Mode::Region && (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d));
     const wtc::PhaseArgs& a = e.pl.a;
+    const bool f32 = d.dtype == WTCONV_F32;
     if (d.L >= 2 && a.PP == 1 && 2 * a.bx * a.by < wtc::kThreads) return false;
-    if (d.dtype == WTCONV_F32) {
-        const int blocks = a.bx * a.by, lanes = ceil_to(blocks, wtc::kThreads);
+    const double fill = (double)d.C * cdiv(d.B, a.PP) / (256 * phase_wgs(d, a, e.pl.rounds));
+    const double enough = f32 || d.L >= 4 ? 1.5 : (d.dtype == WTCONV_F16 ? 0.6 : 0.0);
+    if (d.L >= 2 && ex.mode == Mode::Resident && ex.pl.one_round && fill < enough) return false;
+    if (f32) {
         if (d.L == 1) return true;
-        if (d.k == 3) return d.L == 2 || (d.L == 3 && blocks <= wtc::kThreads);
+        if (d.L > 3 || (ex.mode != Mode::Resident && ex.mode != Mode::Split)) return false;
+        const Plan& pl = ex.pl;
+        const int wgs = std::min(forward_wgs(d, pl.one_round != 0), lds_wgs(pl.lds_floats));
+        if (a.PP * phase_wgs(d, a, e.pl.rounds) < std::min(3, pl.PP * wgs)) return false;
+        double busy;
+        const double ratio = phase_model_ratio(d, a, e.pl.rounds, ex, busy);
+        if (d.k == 3) return (d.L == 2 || e.pl.rounds == 1) && ratio <= (busy >= 0.8 ? 0.9 : (busy >= 0.75 ? 0.95 : 1.4));
+        const int blocks = a.bx * a.by, lanes = ceil_to(blocks, wtc::kThreads);
         const int used = blocks <= wtc::kThreads ? wtc::kThreads / blocks * blocks : blocks;
-        const bool idle = 4 * used <= 3 * lanes;
-        return (d.L == 2 && (idle || edge <= 20)) || (d.L == 3 && idle && edge > 32);
+        const bool idle = 4 * used <= 3 * lanes || (wgs <= 3 && busy <= 0.7);
+        return (d.L == 2 && edge <= 20) || (idle && ratio <= 0.5);
     }
     if (d.L <= 4) return true;
-    return edge >= 48 || (edge <= 32 && (long)d.B * d.C < kSplitMinPlanes);
+    return edge >= 48 || (edge <= 32 && (long)d.B * d.C < kPhaseSmallL5Planes);
 }
 
 // region: always in region tiles (a pass on the first level with a carry).

@@ -208,7 +208,21 @@ def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
     ((8, 64, 116, 116, 5, 2, "f32"), 2), ((8, 64, 128, 128, 3, 3, "f32"), 2), ((8, 64, 134, 134, 5, 2, "f32"), 0),
     ((8, 64, 169, 169, 5, 3, "f32"), 2), ((8, 64, 170, 170, 3, 2, "f32"), 2), ((8, 64, 116, 170, 5, 2, "f32"), 2),
     ((8, 64, 60, 170, 5, 3, "f32"), 2), ((16, 64, 224, 224, 5, 3, "f32"), 0), ((16, 64, 100, 100, 5, 2, "f32"), 0),
-    ((16, 96, 72, 72, 5, 4, "f32"), 0), ((16, 64, 224, 224, 5, 3, "bf16"), 2)])
+    ((16, 96, 72, 72, 5, 4, "f32"), 0), ((16, 64, 224, 224, 5, 3, "bf16"), 2),
+    # few batches
+    ((8, 64, 56, 56, 5, 1, "f16"), 1), ((4, 96, 64, 64, 5, 3, "f16"), 0), ((16, 96, 64, 64, 5, 3, "f16"), 1),
+    ((16, 64, 56, 56, 5, 5, "bf16"), 0), ((48, 64, 56, 56, 5, 5, "bf16"), 1), ((1, 64, 56, 56, 5, 3, "bf16"), 1),
+    ((16, 64, 48, 48, 5, 3, "f32"), 0), ((24, 64, 48, 48, 5, 3, "f32"), 1), ((2, 16, 32, 32, 5, 1, "f32"), 1),
+    # fewer planes per CU than the vector plan
+    ((32, 96, 72, 72, 5, 2, "f32"), 1), ((32, 96, 72, 72, 5, 3, "f32"), 0), ((32, 96, 72, 72, 3, 2, "f32"), 0),
+    ((32, 96, 64, 64, 3, 2, "f32"), 1), ((32, 96, 64, 64, 3, 3, "f32"), 0), ((32, 128, 50, 70, 3, 3, "f32"), 0),
+    # float32, k = 5, L = 2 and 3
+    ((64, 96, 56, 56, 5, 3, "f32"), 0), ((64, 96, 48, 48, 5, 3, "f32"), 1), ((32, 128, 55, 57, 5, 3, "f32"), 1),
+    ((64, 96, 60, 60, 5, 2, "f32"), 1), ((64, 192, 28, 28, 5, 3, "f32"), 0), ((32, 128, 63, 95, 5, 3, "f32"), 1),
+    ((64, 256, 20, 20, 5, 2, "f32"), 1), ((64, 256, 20, 20, 5, 3, "f32"), 0),
+    # float32, k = 3
+    ((64, 192, 28, 28, 3, 3, "f32"), 1), ((64, 192, 32, 32, 3, 2, "f32"), 0), ((32, 128, 35, 90, 3, 2, "f32"), 0),
+    ((64, 128, 40, 40, 3, 2, "f32"), 1), ((32, 128, 55, 57, 3, 3, "f32"), 1), ((32, 128, 63, 95, 3, 3, "f32"), 0)])
 def test_where_the_forward_is_polyphase(phase_routes, spec, route):
     assert phase_routes([spec])[0][0] == route
 
