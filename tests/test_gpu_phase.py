@@ -251,7 +251,9 @@ def plain_forward(x, bw, bs, lw, ls):
 
 @pytest.mark.parametrize("B,C,H,W,k,L,dtype", [
     (3, 2, 57, 55, 5, 1, "f32"), (2, 2, 48, 48, 5, 2, "f32"), (2, 2, 57, 57, 5, 2, "bf16"), (2, 2, 56, 56, 5, 3, "bf16"),
-    (3, 2, 56, 56, 5, 2, "f16"), (20, 3, 13, 19, 3, 4, "bf16"), (2, 1, 130, 128, 5, 1, "bf16"), (2, 2, 120, 160, 3, 3, "f16")])
+    (3, 2, 56, 56, 5, 2, "f16"), (20, 3, 13, 19, 3, 4, "bf16"), (2, 1, 130, 128, 5, 1, "bf16"), (2, 2, 120, 160, 3, 3, "f16"),
+    (17, 390, 17, 14, 5, 2, "f16"), (11, 512, 15, 11, 5, 4, "f16"), (9, 390, 14, 25, 3, 5, "bf16"),
+    (23, 768, 11, 15, 5, 2, "f32"), (15, 768, 24, 13, 5, 3, "f32")])
 def test_infinities_keep_their_sign(B, C, H, W, k, L, dtype):
     """y and dx where a pixel is infinite, and two of opposite sign are close:
     +inf, -inf or NaN as the step-by-step operator has it. (Level kernels
@@ -260,8 +262,10 @@ def test_infinities_keep_their_sign(B, C, H, W, k, L, dtype):
     for w in dev.lw:
         w.abs_()
     inf = float("inf")
-    f64 = lambda v: v.double().cpu()  # noqa: E731
-    params = f64(dev.bw), f64(dev.bs), [f64(w) for w in dev.lw], [f64(s) for s in dev.ls]
+    few = sorted({0, C - 1})  # the channels with infinities
+    f64 = lambda v: v[:, few].double().cpu()  # noqa: E731
+    par = lambda v: v.double().cpu().view(C, -1, *v.shape[1:])[few].flatten(0, 1)  # noqa: E731
+    params = par(dev.bw), par(dev.bs), [par(w) for w in dev.lw], [par(s) for s in dev.ls]
     rotated = params[0].flip(-1, -2), params[1], [w.flip(-1, -2) for w in params[2]], params[3]
     for t in (dev.x, dev.dy):
         t[0, 0, H // 3, W // 2], t[0, 0, H // 3 + 1, W // 2 + 3], t[B - 1, C - 1, H - 1, W - 1] = inf, -inf, -inf
@@ -277,8 +281,8 @@ def test_infinities_keep_their_sign(B, C, H, W, k, L, dtype):
 
 
 @pytest.mark.parametrize("B,C,H,W,k,L,dtype", [(3, 3, 57, 55, 5, 1, "f32"), (2, 3, 56, 56, 5, 3, "bf16"),
-                                               (3, 3, 56, 56, 3, 2, "f16"), (2, 3, 130, 128, 5, 1, "bf16"),
-                                               (3, 3, 7, 7, 5, 1, "bf16")])
+                                               (3, 3, 56, 56, 3, 2, "bf16"), (3, 3, 40, 41, 5, 1, "f16"),
+                                               (2, 3, 130, 128, 5, 1, "bf16"), (3, 3, 7, 7, 5, 1, "bf16")])
 @pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan")])
 def test_non_finite_kernels(B, C, H, W, k, L, dtype, value):
     """One non-finite tap of the base kernel and of a level's band make their
@@ -305,17 +309,17 @@ def test_non_finite_kernels(B, C, H, W, k, L, dtype, value):
     assert torch.equal(torch.nan_to_num(got[:, 0].float(), 0, 1, -1)[bad], torch.nan_to_num(ref, 0, 1, -1)[bad])
 
 
-@pytest.mark.parametrize("H,W,k,L", [(56, 56, 5, 1), (57, 55, 3, 2), (130, 128, 5, 1)])
-def test_float16_kernels_keep_float32_accuracy(H, W, k, L):
+@pytest.mark.parametrize("B,C,H,W,k,L", [(2, 4, 56, 56, 5, 1), (17, 390, 17, 14, 5, 2), (13, 390, 35, 9, 3, 2),
+                                         (2, 4, 130, 128, 5, 1)])
+def test_float16_kernels_keep_float32_accuracy(B, C, H, W, k, L):
     """Taps 2^-34 of the channel's largest, each alone on a pixel: the outputs
     are those of the float32 taps, to half a step of float16."""
     g = torch.Generator(device="cuda").manual_seed(1)
-    C = 4
     bw = (1 + torch.rand(C, k, k, generator=g, device="cuda")) * 2.0 ** -34
     bw[:, k // 2, k // 2] = 1
     one = torch.ones(C, device="cuda")
     lw, ls = [torch.zeros(4 * C, k, k, device="cuda")] * L, [torch.ones(4 * C, device="cuda")] * L
-    x = torch.zeros(2, C, H, W, dtype=torch.float16, device="cuda")
+    x = torch.zeros(B, C, H, W, dtype=torch.float16, device="cuda")
     x[:, :, H // 2, W // 2] = 60000
     y = binding.forward(x, bw, one, lw, ls).double()
     want = torch.nn.functional.conv2d(x.double(), bw.double()[:, None], padding=k // 2, groups=C)
@@ -341,3 +345,42 @@ def test_kernel_gradients_of_deep_levels_have_no_bias(B, C, H, W, k, L, dtype):
         assert float((got - want).norm() / want.norm()) < 1.5e-7
         assert float((got - want).mean((0, 2, 3)).abs().max() / want.pow(2).mean().sqrt()) < 7.5e-8
         x, dy = x[:, :, 0], dy[:, :, 0]
+
+
+# (problem, batches of the forward, of the kernel gradients): planes of a batch,
+# batches of a workgroup and planes in its last, partial one. tests/test_planner.py
+# checks that the library still plans them so.
+GROUPS = [
+    ((34, 390, 15, 11, 3, 1, "bf16"), (12, 3, 10), (17, 2, 17)), ((9, 390, 42, 14, 3, 2, "bf16"), (5, 2, 4), (5, 2, 4)),
+    ((11, 768, 11, 9, 3, 3, "bf16"), (6, 2, 5), (6, 2, 5)), ((20, 390, 17, 10, 3, 4, "f16"), (7, 3, 6), (7, 3, 6)),
+    ((9, 390, 14, 25, 3, 5, "bf16"), (5, 2, 4), (5, 2, 4)), ((43, 390, 14, 10, 5, 1, "bf16"), (15, 3, 13), (22, 2, 21)),
+    ((17, 390, 17, 14, 5, 2, "f16"), (10, 2, 7), (9, 2, 8)), ((29, 390, 13, 9, 5, 3, "bf16"), (8, 4, 5), (8, 4, 5)),
+    ((11, 512, 15, 11, 5, 4, "f16"), (6, 2, 5), (6, 2, 5)), ((9, 390, 13, 28, 5, 5, "bf16"), (7, 2, 2), (5, 2, 4)),
+    ((39, 390, 9, 14, 3, 1, "f32"), (20, 2, 19), None), ((7, 390, 62, 11, 3, 2, "f32"), (4, 2, 3), None),
+    ((5, 390, 61, 9, 3, 3, "f32"), (3, 2, 2), None), ((11, 390, 19, 20, 5, 1, "f32"), (6, 2, 5), None),
+    ((23, 768, 11, 15, 5, 2, "f32"), (8, 3, 7), None), ((15, 768, 24, 13, 5, 3, "f32"), (4, 4, 3), None),
+]
+
+
+@pytest.mark.parametrize("spec,forward,gradient", GROUPS)
+def test_batches_of_planes(spec, forward, gradient):
+    """Several planes to a batch, several batches to a workgroup, the last one
+    partial: y, dx and the kernel gradients."""
+    B, C, H, W, k, L, dtype = spec
+    test_forward_and_dx(B, C, H, W, k, L, dtype)
+    if gradient:
+        test_kernel_gradients(B, C, H, W, k, L, dtype)
+
+
+# polyphase forwards (in region tiles the last) with more than one stage
+STAGES = [(2, 2, 56, 56, 5, 3, "bf16"), (2, 2, 57, 57, 5, 2, "bf16"), (17, 390, 17, 14, 5, 2, "f16"),
+          (11, 512, 15, 11, 5, 4, "f16"), (9, 390, 14, 25, 3, 5, "bf16"), (23, 768, 11, 15, 5, 2, "f32"),
+          (15, 768, 24, 13, 5, 3, "f32"), (5, 390, 61, 9, 3, 3, "f32"), (2, 2, 120, 160, 5, 1, "f16")]
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", STAGES)
+def test_extreme_pixels_of_deeper_stages(B, C, H, W, k, L, dtype):
+    """The two tests above on planes whose stages all run polyphase."""
+    test_non_finite_pixels_reach_their_outputs_only(B, C, H, W, k, L, dtype, float("nan"))
+    test_non_finite_pixels_reach_their_outputs_only(B, C, H, W, k, L, dtype, float("inf"))
+    test_lowest_values_reach_their_outputs_only(B, C, H, W, k, L, dtype)

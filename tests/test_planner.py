@@ -193,6 +193,21 @@ def phase_routes(tmp_path_factory):
     return run
 
 
+def test_gpu_tests_of_the_polyphase_kernels_reach_them(phase_routes):
+    """The problems that tests/test_gpu_phase.py lists for their plans have them."""
+    pytest.importorskip("torch")
+    from tests import test_gpu_phase as gpu
+
+    for (spec, fwd, grad), r in zip(gpu.GROUPS, phase_routes([g[0] for g in gpu.GROUPS])):
+        assert r[:4] == (1, *fwd), (spec, r)
+        assert r[4:] == ((1, *grad) if grad else (0, 0, 0, 0)), (spec, r)
+    assert all(r[0] == (2 if s[2] > 100 else 1) for s, r in zip(gpu.STAGES, phase_routes(gpu.STAGES)))
+    # every stage count, kernel size and type somewhere, in the forward and the gradients
+    reached = {(s[4], s[5], s[6]) for s, f, g in gpu.GROUPS}
+    assert {(k, L) for k, L, t in reached if t != "f32"} == {(k, L) for k in (3, 5) for L in range(1, 6)}
+    assert {(k, L) for k, L, t in reached if t == "f32"} == {(k, L) for k in (3, 5) for L in range(1, 4)}
+
+
 # on both sides of every line of the gradient rule; the times are at the rule
 @pytest.mark.parametrize("spec,phase", [
     ((64, 768, 7, 7, 5, 1, "bf16"), 0), ((128, 768, 7, 7, 5, 1, "bf16"), 1), ((32, 768, 7, 7, 3, 1, "f16"), 1),
