@@ -313,7 +313,8 @@ def test_non_finite_kernels(B, C, H, W, k, L, dtype, value):
                                          (2, 4, 130, 128, 5, 1)])
 def test_float16_kernels_keep_float32_accuracy(B, C, H, W, k, L):
     """Taps 2^-34 of the channel's largest, each alone on a pixel: the outputs
-    are those of the float32 taps, to half a step of float16."""
+    are those of the float32 taps, to half a step of float16 and the bound of the
+    split, 2^-50 of the largest tap (two float16 pieces: 2^-39)."""
     g = torch.Generator(device="cuda").manual_seed(1)
     bw = (1 + torch.rand(C, k, k, generator=g, device="cuda")) * 2.0 ** -34
     bw[:, k // 2, k // 2] = 1
@@ -324,7 +325,7 @@ def test_float16_kernels_keep_float32_accuracy(B, C, H, W, k, L):
     y = binding.forward(x, bw, one, lw, ls).double()
     want = torch.nn.functional.conv2d(x.double(), bw.double()[:, None], padding=k // 2, groups=C)
     want[:, :, H // 2, W // 2] = 60000
-    assert float((y - want).abs().max()) <= 2.0 ** -25 * 1.001
+    assert float((y - want).abs().max()) <= 2.0 ** -25 + 60000 * 2.0 ** -50
 
 
 @pytest.mark.parametrize("B,C,H,W,k,L,dtype", [(64, 12, 56, 56, 5, 3, "bf16"), (64, 12, 48, 48, 5, 5, "bf16"),
