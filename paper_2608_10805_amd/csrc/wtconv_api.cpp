@@ -1516,6 +1516,43 @@ bool phase_f32_tiles_pay(const wtconv_desc& d)
     return 10 * tiled >= 17L * d.H * d.W && choose(d, false).mode == Mode::Region;
 }
 
+// Planes of the batch over those that the rounds of resident workgroups have room
+// for: what a last round that is nearly empty, or a last group of planes, leaves.
+double rounds_fill(long B, long groups, int nchunks, int nb, int wgs)
+{
+    const long grid = nchunks * groups, slots = 256L * wgs;
+    return (double)B * groups / ((double)((grid + slots - 1) / slots) * slots * nb);
+}
+
+// float32 region tiles against the vector kernels' 56 x 56 ones. With a carry
+// (phase_f32_tiles_pay()) only the rounds' fill is left to ask for (polyphase /
+// vector training step, fills in brackets): 69 x 102 B18 C136 (0.53, 0.64) 1.05, 60
+// x 170 C64 B1 (0.25, 0.5) 1.04, 169 x 169 B1 C64 k3 (0.50, 1.0) 1.05; 128 x 128 B2
+// C64 k3 (0.50, 0.56) 0.97, 113 x 113 B9 C70 (0.74) 0.88. At L = 1, polyphase /
+// vector forward by the padded areas' ratio times the fill: one or two planes per
+// tile do not make up for its weight tables below 1 (k = 5: 224 x 224 B1 C144 0.75
+// 1.15, 112 x 112 B1 C144 0.56 1.05, 148 x 148 B1 C144 0.59 1.10; 320 x 320 B1 C96
+// 1.05 1.02; 80 x 120 B4 C64 1.8 0.68), at k = 3 below 0.78 (224 x 224 B1 0.75 1.08,
+// 168 x 168 B1 C64 0.44 1.21; 148 x 148 B1 0.79 0.93); from three on 0.65 will do
+// (224 x 224 B4 k5 0.75 0.94; k3 B8 C64 0.67 0.88) where the tiles pad no more than
+// the vector ones (168 x 168, 1.14 and 1.0: k5 B8 C64 1.14, k3 B16 C96 1.23, k3 B26
+// C40 step 1.07).
+bool phase_f32_region_pays(const wtconv_desc& d, const PhasePlan& pl, bool carry)
+{
+    const wtc::PhaseArgs& a = pl.a;
+    const int tiles = a.rg_ntx * a.rg_nty;
+    const double fill = rounds_fill(d.B, (long)d.C * tiles, pl.nchunks, a.nb, phase_wgs(d, a, 2));
+    if (carry) {
+        const RegionPlan rp = choose(d, false).rp;
+        const double vec_fill = rounds_fill(d.B, (long)d.C * rp.ntx * rp.nty, rp.pl.nchunks, rp.pl.nb, 4);
+        return fill >= 0.6 || (fill >= 0.5 && fill >= 0.85 * vec_fill);
+    }
+    const double vec = 56.0 * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
+    const double pad = vec / ((double)tiles * a.rg_th * a.rg_tw);
+    if (a.nb >= 3 && pad >= 0.95) return pad * fill >= 0.65;
+    return pad >= 1.03 && pad * fill >= (d.k == 3 ? 0.78 : 1.0);
+}
+
 // Lane-cycles per plane of the two forwards as their planners model them,
 // polyphase over vector (whose general variant runs at 3/4 of the single-round
 // one); `busy`: how much of a CU's lanes the vector plan fills.
@@ -1529,9 +1566,32 @@ double phase_model_ratio(const wtconv_desc& d, const wtc::PhaseArgs& a, int roun
     return phase_cycles(d, a, rounds) / a.PP / phase_wgs(d, a, rounds) / issue * (mixed || pl.one_round ? 1.0 : 0.75);
 }
 
+// float32, L = 1, both kernels over whole planes: the model ratio with each side's
+// fill of its rounds. The general vector variant is always the slower one.
+// Polyphase / vector forward by that figure: one round k = 5 0.23 (64 x 64 B64 C96)
+// 0.90, 0.34 (40 x 40 B64 C128) 0.94, 0.42 and 0.47 (56 x 56 and 64 x 64 B16 C64)
+// 1.03 and 1.09; k = 3 0.55 0.87-0.97, 0.75 (40 x 40 B64 C128) 0.93, 0.82 (56 x 56
+// B16 C128) 1.05, 0.96 (64 x 64 B16 C64) 1.13; two rounds mixed in one launch k = 5
+// 0.22 (12 x 16) 0.78, 0.35 (16 x 16 B64 C96) 1.07, 0.51 (B64 C256) 1.11; k = 3 0.66
+// 0.94-1.0, 0.81 0.99 (step 1.10-1.15), 1.09 1.02-1.08; eight batches of planes and
+// more make up for it there (14 x 12 B128 C435 0.46 and 0.97: 0.84, 0.75).
+bool phase_f32_one_level_pays(const wtconv_desc& d, const PhasePlan& pp, const Exec& ex)
+{
+    const Plan& pl = ex.pl;
+    const bool mixed = pl.mx.rounds > 0;
+    if (!mixed && !pl.one_round) return true;
+    if (mixed && pp.a.nb >= 8 * pp.a.PP) return true;
+    double busy;
+    const int wgs = std::min(4, mixed ? lds_wgs(pl.lds_floats) : std::min(forward_wgs(d, true), lds_wgs(pl.lds_floats)));
+    const double fill = rounds_fill(d.B, d.C, pl.nchunks, pl.nb, wgs);
+    const double ratio = phase_model_ratio(d, pp.a, pp.rounds, ex, busy) * fill /
+                         rounds_fill(d.B, d.C, pp.nchunks, pp.a.nb, phase_wgs(d, pp.a, pp.rounds));
+    return ratio <= (mixed ? (d.k == 3 ? 0.7 : 0.3) : (d.k == 3 ? 0.75 : 0.4));
+}
+
 // Where the polyphase forward is the faster one. Measured on MI355X against the
 // vector kernels (polyphase / vector, k = 5 and 3):
-//  - float32, L = 1: forward 0.61 (63 x 95) to 1.01, training step 0.76 to 1.01;
+//  - float32, L = 1: phase_f32_one_level_pays(), phase_f32_region_pays();
 //    16-bit storage, L <= 4: forward 0.30 (63 x 95 L1) to 0.99, most 0.45-0.75;
 //  - few batches of planes for the workgroups that are resident at once do not
 //    make up for the weight tables, formed in float64, against a vector plan of
@@ -1550,7 +1610,8 @@ double phase_model_ratio(const wtconv_desc& d, const wtc::PhaseArgs& a, int roun
 //    their lanes idle (60 x 60 L2 0.87; 55 x 57 L3 0.91; 32 x 32 L3 0.90; 44 x 44
 //    0.95, 0.94), while the model gives it half of the vector kernels' time (28 x
 //    28 0.51 and 0.59: 0.99; 31 x 47 L3 0.61: 1.11), and on the smallest planes at
-//    L = 2 (20 x 20 0.97, 14 x 14 0.96);
+//    L = 2 (20 x 20 0.97, 14 x 14 0.96) if the last round is not half empty (14 x 12
+//    B128 C435, 435 workgroups in 768 places: 1.05);
 //  - at k = 3 where the model ratio is at most 1.4 (28 x 28 L3 1.26: 0.99; 24 x 24
 //    L2 1.33: 0.90; 35 x 90 L3 1.46: 1.08), 0.95 if the vector lanes are 75 % full
 //    (40 x 40 L2 0.91: 0.96; 32 x 32 L2 1.01 and L3 1.26: 1.01-1.04) and 0.9 at 80 %
@@ -1574,7 +1635,8 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
     const int edge = std::max(d.H, d.W);
     const Exec ex = choose(d, false);
     if (e.kind == PhaseExec::Region)
-        return ex.mode == Mode::Region && (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d));
+        return ex.mode == Mode::Region && (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d)) &&
+               (d.dtype != WTCONV_F32 || phase_f32_region_pays(d, e.pl, d.L >= 2));
     const wtc::PhaseArgs& a = e.pl.a;
     const bool f32 = d.dtype == WTCONV_F32;
     if (d.L >= 2 && a.PP == 1 && 2 * a.bx * a.by < wtc::kThreads) return false;
@@ -1582,7 +1644,7 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
     const double enough = f32 || d.L >= 4 ? 1.5 : (d.dtype == WTCONV_F16 ? 0.6 : 0.0);
     if (d.L >= 2 && ex.mode == Mode::Resident && ex.pl.one_round && fill < enough) return false;
     if (f32) {
-        if (d.L == 1) return true;
+        if (d.L == 1) return ex.mode != Mode::Resident || phase_f32_one_level_pays(d, e.pl, ex);
         if (d.L > 3 || (ex.mode != Mode::Resident && ex.mode != Mode::Split)) return false;
         const Plan& pl = ex.pl;
         const int wgs = std::min(forward_wgs(d, pl.one_round != 0), lds_wgs(pl.lds_floats));
@@ -1593,7 +1655,8 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
         const int blocks = a.bx * a.by, lanes = ceil_to(blocks, wtc::kThreads);
         const int used = blocks <= wtc::kThreads ? wtc::kThreads / blocks * blocks : blocks;
         const bool idle = 4 * used <= 3 * lanes || (wgs <= 3 && busy <= 0.7);
-        return (d.L == 2 && edge <= 20) || (idle && ratio <= 0.5);
+        const double fill = rounds_fill(d.B, d.C, e.pl.nchunks, a.nb, phase_wgs(d, a, e.pl.rounds));
+        return (d.L == 2 && edge <= 20 && (fill >= 0.8 || a.nb <= 3 * a.PP)) || (idle && ratio <= 0.5);
     }
     if (d.L <= 4) return true;
     return edge >= 48 || (edge <= 32 && (long)d.B * d.C < kPhaseSmallL5Planes);
@@ -1621,7 +1684,9 @@ PhaseExec choose_phase(const wtconv_desc& d, int skip_base, bool region = false)
             e.kind = PhaseExec::Resident;
         else if (make_phase_region_plan(d, e.pl))
             e.kind = PhaseExec::Region;
-        return region || phase_pays(d, e) ? e : none;
+        if (region)
+            return d.dtype != WTCONV_F32 || phase_f32_region_pays(d, e.pl, true) ? e : none;
+        return phase_pays(d, e) ? e : none;
     });
 }
 

@@ -357,8 +357,8 @@ GROUPS = [
     ((9, 390, 14, 25, 3, 5, "bf16"), (5, 2, 4), (5, 2, 4)), ((43, 390, 14, 10, 5, 1, "bf16"), (15, 3, 13), (22, 2, 21)),
     ((17, 390, 17, 14, 5, 2, "f16"), (10, 2, 7), (9, 2, 8)), ((29, 390, 13, 9, 5, 3, "bf16"), (8, 4, 5), (8, 4, 5)),
     ((11, 512, 15, 11, 5, 4, "f16"), (6, 2, 5), (6, 2, 5)), ((9, 390, 13, 28, 5, 5, "bf16"), (7, 2, 2), (5, 2, 4)),
-    ((39, 390, 9, 14, 3, 1, "f32"), (20, 2, 19), None), ((7, 390, 62, 11, 3, 2, "f32"), (4, 2, 3), None),
-    ((5, 390, 61, 9, 3, 3, "f32"), (3, 2, 2), None), ((11, 390, 19, 20, 5, 1, "f32"), (6, 2, 5), None),
+    ((33, 390, 11, 9, 3, 1, "f32"), (17, 2, 16), None), ((7, 390, 62, 11, 3, 2, "f32"), (4, 2, 3), None),
+    ((5, 390, 61, 9, 3, 3, "f32"), (3, 2, 2), None), ((19, 390, 19, 7, 5, 1, "f32"), (10, 2, 9), None),
     ((23, 768, 11, 15, 5, 2, "f32"), (8, 3, 7), None), ((15, 768, 24, 13, 5, 3, "f32"), (4, 4, 3), None),
 ]
 
@@ -371,6 +371,17 @@ def test_batches_of_planes(spec, forward, gradient):
     test_forward_and_dx(B, C, H, W, k, L, dtype)
     if gradient:
         test_kernel_gradients(B, C, H, W, k, L, dtype)
+
+
+# float32 in region tiles: one level, and a carry from the coarser ones
+REGIONS = [(1, 96, 115, 113, 5, 1, "f32"), (1, 103, 116, 113, 3, 1, "f32"), (2, 64, 97, 69, 5, 3, "f32"),
+           (3, 64, 123, 59, 3, 3, "f32")]
+
+
+@pytest.mark.parametrize("B,C,H,W,k,L,dtype", REGIONS)
+def test_float32_region_tiles(B, C, H, W, k, L, dtype):
+    test_forward_and_dx(B, C, H, W, k, L, dtype)
+    test_extreme_pixels_of_deeper_stages(B, C, H, W, k, L, dtype)
 
 
 # polyphase forwards (in region tiles the last) with more than one stage

@@ -202,6 +202,7 @@ def test_gpu_tests_of_the_polyphase_kernels_reach_them(phase_routes):
         assert r[:4] == (1, *fwd), (spec, r)
         assert r[4:] == ((1, *grad) if grad else (0, 0, 0, 0)), (spec, r)
     assert all(r[0] == (2 if s[2] > 100 else 1) for s, r in zip(gpu.STAGES, phase_routes(gpu.STAGES)))
+    assert all(r[0] == 2 for r in phase_routes(gpu.REGIONS))
     # every stage count, kernel size and type somewhere, in the forward and the gradients
     reached = {(s[4], s[5], s[6]) for s, f, g in gpu.GROUPS}
     assert {(k, L) for k, L, t in reached if t != "f32"} == {(k, L) for k in (3, 5) for L in range(1, 6)}
@@ -224,6 +225,12 @@ def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
     ((8, 64, 169, 169, 5, 3, "f32"), 2), ((8, 64, 170, 170, 3, 2, "f32"), 2), ((8, 64, 116, 170, 5, 2, "f32"), 2),
     ((8, 64, 60, 170, 5, 3, "f32"), 2), ((16, 64, 224, 224, 5, 3, "f32"), 0), ((16, 64, 100, 100, 5, 2, "f32"), 0),
     ((16, 96, 72, 72, 5, 4, "f32"), 0), ((16, 64, 224, 224, 5, 3, "bf16"), 2),
+    ((18, 136, 69, 102, 5, 3, "f32"), 0), ((1, 64, 169, 169, 3, 2, "f32"), 0), ((2, 64, 128, 128, 3, 2, "f32"), 2),
+    # float32, L = 1
+    ((1, 144, 224, 224, 5, 1, "f32"), 0), ((4, 144, 224, 224, 5, 1, "f32"), 2), ((1, 144, 148, 148, 5, 1, "f32"), 0),
+    ((1, 144, 148, 148, 3, 1, "f32"), 2), ((26, 40, 168, 168, 3, 1, "f32"), 0), ((4, 64, 80, 120, 5, 1, "f32"), 2),
+    ((16, 64, 64, 64, 5, 1, "f32"), 0), ((64, 96, 64, 64, 5, 1, "f32"), 1), ((16, 64, 56, 56, 3, 1, "f32"), 0),
+    ((64, 96, 16, 16, 5, 1, "f32"), 0), ((64, 192, 12, 16, 5, 1, "f32"), 1), ((128, 435, 14, 12, 5, 1, "f32"), 1),
     # few batches
     ((8, 64, 56, 56, 5, 1, "f16"), 1), ((4, 96, 64, 64, 5, 3, "f16"), 0), ((16, 96, 64, 64, 5, 3, "f16"), 1),
     ((16, 64, 56, 56, 5, 5, "bf16"), 0), ((48, 64, 56, 56, 5, 5, "bf16"), 1), ((1, 64, 56, 56, 5, 3, "bf16"), 1),
@@ -235,6 +242,7 @@ def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
     ((64, 96, 56, 56, 5, 3, "f32"), 0), ((64, 96, 48, 48, 5, 3, "f32"), 1), ((32, 128, 55, 57, 5, 3, "f32"), 1),
     ((64, 96, 60, 60, 5, 2, "f32"), 1), ((64, 192, 28, 28, 5, 3, "f32"), 0), ((32, 128, 63, 95, 5, 3, "f32"), 1),
     ((64, 256, 20, 20, 5, 2, "f32"), 1), ((64, 256, 20, 20, 5, 3, "f32"), 0),
+    ((128, 384, 14, 14, 5, 2, "f32"), 1), ((128, 435, 14, 12, 5, 2, "f32"), 0),
     # float32, k = 3
     ((64, 192, 28, 28, 3, 3, "f32"), 1), ((64, 192, 32, 32, 3, 2, "f32"), 0), ((32, 128, 35, 90, 3, 2, "f32"), 0),
     ((64, 128, 40, 40, 3, 2, "f32"), 1), ((32, 128, 55, 57, 3, 3, "f32"), 1), ((32, 128, 63, 95, 3, 3, "f32"), 0)])
