@@ -1167,8 +1167,10 @@ bool phase_grad_offered(const wtconv_desc& d)
     // 16-bit storage: one exact product per term. (float32 needs six, took as
     // long as the vector kernels, 56 x 56 B64 C96 L3 training step 230 against
     // 205 us, and its longer chains lost a factor of two in the error.)
-    return wtc::launch_phase_grad && d.dtype != WTCONV_F32 && (d.k == 3 || d.k == 5) && d.L >= 1 && d.L <= wtc::kPhaseMaxStages && d.W >= 4 &&
-           (!use_tiny(d) || d.L == 1);  // tiny planes: L = 1 alone (training step 7 x 7 B128 C768 71 -> 58 us, L2 79 -> 96)
+    return wtc::launch_phase_grad && d.dtype != WTCONV_F32 && (d.k == 3 || d.k == 5) && d.L >= 1 &&
+           d.L <= wtc::kPhaseMaxStages && d.W >= 4 &&
+           // tiny planes: L = 1 alone (training step 7 x 7 B128 C768 71 -> 58 us, L2 79 -> 96)
+           (!use_tiny(d) || d.L == 1);
 }
 
 // Planes of at most 8 x 8 have the one-plane-per-lane kernel. At L = 1 in 16
@@ -1400,63 +1402,65 @@ bool make_phase_plan(const wtconv_desc& d, PhasePlan& out)
     double best = -1;
     const long HW = (long)d.H * d.W;
     for (int PP = 1; PP <= std::min(d.B, 32); ++PP)
-      for (int fw = d.L > 1 ? 3 : 4; fw >= (d.L > 2 ? 2 : (d.L > 1 ? 3 : 4)); --fw) {
-        if (((PP - 1L) * d.C + 1) * HW >= 1L << 29) break;  // 32-bit byte offsets within a batch
-        PhasePlan pp;
-        wtc::PhaseArgs& a = pp.a;
-        memset(&a, 0, sizeof(a));
-        a.B = d.B;
-        a.C = d.C;
-        a.H = d.H;
-        a.W = d.W;
-        a.L = d.L;
-        a.PP = PP;
-        a.fine_waves = fw;
-        a.bx = ceil_to(d.W, 4) / 4;
-        a.by = ceil_to(d.H, 4) / 4;
-        const long blocks = (long)PP * a.bx * a.by;
-        if (blocks > 2 * wtc::kThreads) break;
-        pp.rounds = blocks > wtc::kThreads ? 2 : 1;
-        int h = d.H, w = d.W;
-        bool ok = true;
-        for (int s = 0; s < d.L && ok; ++s) {
-            wtc::PhaseStage& g = a.st[s];
-            g.h = h;
-            g.w = w;
-            g.ct = ceil_to(w, 8) / 8;
-            const int jt = (h + 1) / 2;
-            if (s == 0) {
-                g.V = 16 * a.fine_waves / (PP * g.ct);
-                ok = g.V >= 1;
-                if (!ok) break;
-                g.js = cdiv(jt, g.V);
-                g.V = cdiv(jt, g.js);
-                ok = g.js <= wtc::phase_max_js(pp.rounds);
-            } else {
-                double bc = -1;
-                if (jt <= 2) {  // one run per column of tiles, over the plane's own rows
-                    g.js = jt;
-                    g.V = 1;
-                } else for (int js : {1, 2, 4}) {
-                    const int V = cdiv(jt, js);
-                    const double c = cdiv(PP * V * g.ct, 16) * (16.0 * js * d.k * 6 + 200);
-                    if (bc < 0 || c < bc) {
-                        bc = c;
-                        g.js = js;
-                        g.V = V;
+        for (int fw = d.L > 1 ? 3 : 4; fw >= (d.L > 2 ? 2 : (d.L > 1 ? 3 : 4)); --fw) {
+            if (((PP - 1L) * d.C + 1) * HW >= 1L << 29) break;  // 32-bit byte offsets within a batch
+            PhasePlan pp;
+            wtc::PhaseArgs& a = pp.a;
+            memset(&a, 0, sizeof(a));
+            a.B = d.B;
+            a.C = d.C;
+            a.H = d.H;
+            a.W = d.W;
+            a.L = d.L;
+            a.PP = PP;
+            a.fine_waves = fw;
+            a.bx = ceil_to(d.W, 4) / 4;
+            a.by = ceil_to(d.H, 4) / 4;
+            const long blocks = (long)PP * a.bx * a.by;
+            if (blocks > 2 * wtc::kThreads) break;
+            pp.rounds = blocks > wtc::kThreads ? 2 : 1;
+            int h = d.H, w = d.W;
+            bool ok = true;
+            for (int s = 0; s < d.L && ok; ++s) {
+                wtc::PhaseStage& g = a.st[s];
+                g.h = h;
+                g.w = w;
+                g.ct = ceil_to(w, 8) / 8;
+                const int jt = (h + 1) / 2;
+                if (s == 0) {
+                    g.V = 16 * a.fine_waves / (PP * g.ct);
+                    ok = g.V >= 1;
+                    if (!ok) break;
+                    g.js = cdiv(jt, g.V);
+                    g.V = cdiv(jt, g.js);
+                    ok = g.js <= wtc::phase_max_js(pp.rounds);
+                } else {
+                    double bc = -1;
+                    if (jt <= 2) {  // one run per column of tiles, over the plane's own rows
+                        g.js = jt;
+                        g.V = 1;
+                    } else {
+                        for (int js : {1, 2, 4}) {
+                            const int V = cdiv(jt, js);
+                            const double c = cdiv(PP * V * g.ct, 16) * (16.0 * js * d.k * 6 + 200);
+                            if (bc < 0 || c < bc) {
+                                bc = c;
+                                g.js = js;
+                                g.V = V;
+                            }
+                        }
                     }
                 }
+                h = (h + 1) / 2;
+                w = (w + 1) / 2;
             }
-            h = (h + 1) / 2;
-            w = (w + 1) / 2;
+            if (!ok || !phase_layout(d, a)) continue;
+            const double score = phase_chunks(d, pp, 1);
+            if (best < 0 || score < best) {
+                best = score;
+                out = pp;
+            }
         }
-        if (!ok || !phase_layout(d, a)) continue;
-        const double score = phase_chunks(d, pp, 1);
-        if (best < 0 || score < best) {
-            best = score;
-            out = pp;
-        }
-    }
     return best >= 0;
 }
 
@@ -1651,7 +1655,8 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
         if (a.PP * phase_wgs(d, a, e.pl.rounds) < std::min(3, pl.PP * wgs)) return false;
         double busy;
         const double ratio = phase_model_ratio(d, a, e.pl.rounds, ex, busy);
-        if (d.k == 3) return (d.L == 2 || e.pl.rounds == 1) && ratio <= (busy >= 0.8 ? 0.9 : (busy >= 0.75 ? 0.95 : 1.4));
+        if (d.k == 3)
+            return (d.L == 2 || e.pl.rounds == 1) && ratio <= (busy >= 0.8 ? 0.9 : (busy >= 0.75 ? 0.95 : 1.4));
         const int blocks = a.bx * a.by, lanes = ceil_to(blocks, wtc::kThreads);
         const int used = blocks <= wtc::kThreads ? wtc::kThreads / blocks * blocks : blocks;
         const bool idle = 4 * used <= 3 * lanes || (wgs <= 3 && busy <= 0.7);

@@ -3,12 +3,14 @@
 // kernels. Internal; not part of the public ABI.
 //
 // Operands. The matrix cores take 16-bit operands and accumulate in float32.
-// A float32 value is split exactly into three bfloat16 pieces h + m + l (8
-// bits each), and a product keeps the six piece products down to 2^-16 of it;
-// the dropped ones are below 2^-24 together, about one float32 rounding.
-// bfloat16 and float16 storage needs one piece for the input itself (bfloat16 /
-// float16 matrix instructions) and three for the float32 weights; the block
-// means of deeper stages are split in three.
+// A float32 value is split into three bfloat16 pieces h + m + l (8 bits each,
+// exactly from 2^-110 on), and a product keeps the six piece products down to
+// 2^-16 of it; the dropped ones are below 2^-24 together, about one float32
+// rounding. bfloat16 and float16 storage needs one piece for the input itself
+// (bfloat16 / float16 matrix instructions) and three for the float32 weights;
+// the block means of deeper stages are split in three. The matrix instructions
+// round their sums down: an error of one direction, which the kernel gradients
+// have to cancel (see wtconv_phase_grad.hip).
 #pragma once
 
 #include <type_traits>
@@ -130,7 +132,8 @@ DEV void mask_raw(int H, int W, int y0, int x0, int edge, RawBlock<ST>& v)
     if constexpr (sizeof(ST) == 4) {
         auto shift = [&](int r, auto e) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v.w[r][c] = shifted ? (c + e.value < 4 ? v.w[r][(c + e.value) & 3] : 0u) : v.w[r][c];
+            for (int c = 0; c < 4; ++c)
+                v.w[r][c] = shifted ? (c + e.value < 4 ? v.w[r][(c + e.value) & 3] : 0u) : v.w[r][c];
         };
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

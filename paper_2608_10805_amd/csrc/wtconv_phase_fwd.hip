@@ -19,19 +19,22 @@
 // third of the vector kernels' VALU instructions remain (splitting the
 // pixels, addresses, the epilogue). Tiles of 16 columns would be 42 % full; a
 // run of row pairs keeps its sums in registers and reads each window row
-// once. 16-bit storage (one or two operand pairs per term) ends up between
-// the VALU and HBM: 56 x 56 B128 C96 L1 bf16 115 -> 51 us (3.0 TB/s of
-// algorithmic traffic), 63 x 95 B32 C128 L3 150 -> 73. In float32 (six pairs)
-// matrix and VALU time are about equal and share the SIMDs: 56 x 56 B64 C96 L3
-// 66.8 -> 63.1, 63 x 95 L3 138 -> 91 (one launch, rows of odd width in whole
-// 16-byte loads), 128 x 128 B8 C64 L1 44.6 -> 27.
+// once. 16-bit storage (three operand pairs per term: the weight's pieces) ends
+// up between the VALU and HBM, vector / polyphase on one card: 56 x 56 B128 C96
+// L1 bf16 94.5 -> 48 us (3.2 TB/s of algorithmic traffic), L3 118 -> 77, L5 133
+// -> 113, 63 x 95 B32 C128 L3 142 -> 70. float16 sums its pieces in two passes
+// and pays for it in registers: 56 x 56 B128 C96 L1 89 -> 44, 256 x 256 B8 C128
+// L3 371 -> 233. In float32 (six pairs) matrix and VALU time are about equal and
+// share the SIMDs: 63 x 95 L3 127 -> 87 (one launch, rows of odd width in whole
+// 16-byte loads), 48 x 48 B64 C96 L3 60 -> 49, 128 x 128 B8 C64 L1 42 -> 30.
 //
 // A tile's window holds zeros of the weight matrix next to its taps, and
 // 0 * inf is NaN: a non-finite input pixel would reach every output of the
 // tiles whose window holds it. Such pixels are zeroed and marked as they are
 // loaded, and the outputs that depend on one, and only they, become NaN. Where
-// one was an infinity (or a kernel of the channel is not finite), the workgroup goes over these outputs once more at its
-// end: an infinity remains where every term of it has the same sign.
+// one was an infinity (or a kernel of the channel is not finite), the workgroup
+// goes over these outputs once more at its end: an infinity remains where every
+// term of it has the same sign.
 #include "wtconv_phase.h"
 
 namespace wtc {
@@ -55,7 +58,8 @@ DEV void coarse_stage_js(const PhaseArgs& a, char* lds, int s, bool carry, int l
         const int v = fdiv(rem, g.r_ct), I = rem - v * g.ct;
         char* plane = lds + a.planes_off + p * a.plane_bytes;
         const int J0 = v * JS;
-        const int bp = a.planes_off + p * a.plane_bytes + g.poff + 2 * ((2 * J0 + M - 2 * R + (grp >> 1)) * g.pitch + 8 * I + 8 * (grp & 1));
+        const int bp = a.planes_off + p * a.plane_bytes + g.poff +
+                       2 * ((2 * J0 + M - 2 * R + (grp >> 1)) * g.pitch + 8 * I + 8 * (grp & 1));
         f32x4 acc[JS];
 #pragma unroll
         for (int J = 0; J < JS; ++J) {
@@ -297,7 +301,8 @@ DEV int nonfinite_terms(const PhaseArgs& a, int c, float f, int py, int px, int 
         const bool ny = ((py ^ y) >> (l - 1)) & 1, nx = ((px ^ x) >> (l - 1)) & 1;
 #pragma unroll 1
         for (int q = 0; q < 4; ++q)
-            add(a.p.lw[l - 1] + (long)(4 * c + q) * KK, a.p.ls[l - 1] + 4 * c + q, dy, dx, ((q & 1) && ny) != ((q >> 1) && nx));
+            add(a.p.lw[l - 1] + (long)(4 * c + q) * KK, a.p.ls[l - 1] + 4 * c + q, dy, dx,
+                ((q & 1) && ny) != ((q >> 1) && nx));
     }
     return cls;
 }
@@ -316,7 +321,8 @@ DEV int weight_terms(const PhaseArgs& a, int c, const ST* __restrict__ plane, in
     for (int e = a.skip_base ? KK : 0; e < (1 + 4 * a.L) * KK && cls != 3; ++e) {
         const int r = e / KK, tap = e - r * KK, l = (r + 3) / 4, q = (r + 3) & 3;
         const int t = a.p.rot ? KK - 1 - tap : tap, ch = 4 * c + q;
-        const float g = l == 0 ? a.p.s0[c] * a.p.w0[(long)c * KK + t] : a.p.ls[l - 1][ch] * a.p.lw[l - 1][(long)ch * KK + t];
+        const float g = l == 0 ? a.p.s0[c] * a.p.w0[(long)c * KK + t]
+                               : a.p.ls[l - 1][ch] * a.p.lw[l - 1][(long)ch * KK + t];
         const bool finite = __builtin_fabsf(g) < __builtin_inff();
         if (finite && !skip) continue;
         const int j = (y >> l) + tap / K - R, i = (x >> l) + tap % K - R;
@@ -388,11 +394,13 @@ DEV void restore_infinities(const PhaseArgs& a, int wave)
             open |= 1u << e;
             float extra = bias;
             if (RGN && a.carry)
-                extra += 0.5f * to_f32(reinterpret_cast<const ST*>(a.carry)[(pl * a.carry_H + (yy >> 1)) * a.carry_W + (xx >> 1)]);
+                extra += 0.5f * to_f32(reinterpret_cast<const ST*>(
+                                    a.carry)[(pl * a.carry_H + (yy >> 1)) * a.carry_W + (xx >> 1)]);
             int cls = 0;
             if (!finite) {
                 cls = weight_terms<K, ST>(a, c, ip, yy, xx, extra);
-                if (cls == 0 && __builtin_fabsf(extra) < __builtin_inff()) op[(long)yy * a.W + xx] = from_f32<ST>(extra);
+                if (cls == 0 && __builtin_fabsf(extra) < __builtin_inff())
+                    op[(long)yy * a.W + xx] = from_f32<ST>(extra);
             }
             if ((cls & 1) || !(extra < __builtin_inff())) pos |= 1u << e;
             if ((cls & 2) || !(extra > -__builtin_inff())) neg |= 1u << e;
@@ -415,7 +423,8 @@ DEV void restore_infinities(const PhaseArgs& a, int wave)
                            (0x11111111u * ((0xfu << xl) & (0xfu >> (3 - xh))));
 #pragma unroll 1
                 for (; left != 0; left &= left - 1) {
-                    const int e = __builtin_ctz(left), cls = nonfinite_terms<K>(a, c, v, py, px, y + 2 * (e >> 2), x + (e & 3));
+                    const int e = __builtin_ctz(left);
+                    const int cls = nonfinite_terms<K>(a, c, v, py, px, y + 2 * (e >> 2), x + (e & 3));
                     pos |= (uint32_t)(cls & 1) << e;
                     neg |= (uint32_t)(cls >> 1) << e;
                 }
@@ -528,7 +537,7 @@ __global__ void __launch_bounds__(kThreads, (phase_waves<K, ST, NR>())) phase_ke
     }
 
     // Stage 0's table only lives until its fragments are in registers: it
-    // borrows the planes' area (the tap-by-tap path takes the weights anew).
+    // borrows the planes' area (restore_infinities() takes the weights anew).
     char* tab0 = lds + a.planes_off;
     double* st = reinterpret_cast<double*>(tab0 + 2 * SC::NW * tab_rows<K, true>() * kPhaseTabPitch);
     const bool finite = stage_kernels<K>(a.p, c, a.L, st, tid);

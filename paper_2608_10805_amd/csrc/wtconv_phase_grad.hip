@@ -22,11 +22,19 @@
 // would take six). The vector pass is bound by FMA issue (56 x 56 B128 C96 L1
 // bf16 104 us); here stage 0 is 10 matrix instructions per 512 pixels and the
 // pass is bound by building the deeper stages (means, splits) and, at L >= 3,
-// by the wavefront of stage 1. Training steps, vector / polyphase gradient
-// pass: 56 x 56 B128 C96 bf16 L1 206 -> 130 us, L3 311 -> 237, L5 435 -> 401;
-// 14 x 14 B128 C384 L2 164 -> 98; 63 x 95 B32 C128 L3 360 -> 220; 224 x 224 B16
-// C64 L1 (region tiles) 349 -> 214. Error of the kernel gradients against 64
-// bits 0.8-1.7e-7 (vector pass 1.1-2.6e-7); L5 3.5e-7 (3.7e-7).
+// by the wavefront of stage 1. Training steps, vector / polyphase kernels on one
+// card: 56 x 56 B128 C96 bf16 L1 287 -> 121 us, L3 397 -> 236, L5 471 -> 400; 14 x
+// 14 B128 C384 L2 214 -> 101; 63 x 95 B32 C128 L3 477 -> 206; 224 x 224 B16 C64 L1
+// (region tiles) 469 -> 210.
+//
+// The matrix instructions round their sums down, and a tap adds up many of them
+// (the LL band 64): the odd rows of x are stored negated, so that half of the
+// errors point up. Error of the kernel gradients against 64 bits 0.6-1.4e-7
+// (vector pass 1.1-3.5e-7); 56 x 56 B128 C96 L3 levels 2 and 3 3.6e-7 and 4.1e-7
+// without it, 1.2e-7 and 0.9e-7 with it (vector pass 3.5e-7 and 1.2e-7).
+//
+// The stages hold non-finite values as zeros; the workgroup sums the planes that
+// have any once more at its end, tap by tap (plain_sum()).
 #include "wtconv_phase.h"
 
 namespace wtc {
@@ -163,7 +171,8 @@ DEV void put_side(const PhaseSide& g, int L, int w2, char* plane, int y0, int x0
 #pragma unroll
     for (int r = 0; r < 4; ++r)
         *reinterpret_cast<uint2*>(o + 2 * r * g.pitch[0]) =
-            X && r % 2 ? make_uint2(raw.w[r][0] ^ 0x80008000u, raw.w[r][1] ^ 0x80008000u) : make_uint2(raw.w[r][0], raw.w[r][1]);
+            X && r % 2 ? make_uint2(raw.w[r][0] ^ 0x80008000u, raw.w[r][1] ^ 0x80008000u)
+                       : make_uint2(raw.w[r][0], raw.w[r][1]);
     if constexpr (!DEEP) return;
     float v[4][4];
     raw_values<ST>(raw, v);
@@ -301,7 +310,8 @@ DEV float plain_sum(const ST* __restrict__ x, const ST* __restrict__ dy, int H, 
                     for (int i = i0; i < i1; ++i) {
                         const int v = i + t - R;
                         const bool in = row && v >= 0 && v < w;
-                        const double d = to_f32(db[(long)j * W + i]), m = to_f32(xb[(long)min(max(u, 0), h - 1) * W + min(max(v, 0), w - 1)]);
+                        const double d = to_f32(db[(long)j * W + i]);
+                        const double m = to_f32(xb[(long)min(max(u, 0), h - 1) * W + min(max(v, 0), w - 1)]);
                         if (in || halo) sum += d * (in ? m : 0.0);
                     }
                 } else {

@@ -114,7 +114,8 @@ variable_list backward_in_python(const Tensor& x, const Tensor& dy, const Tensor
 {
     py::gil_scoped_acquire gil;
     try {
-        const py::object r = py::reinterpret_borrow<py::object>(python_path)(x, dy, bw, bs, bias, levels, need_dx, need_db);
+        const py::object r =
+            py::reinterpret_borrow<py::object>(python_path)(x, dy, bw, bs, bias, levels, need_dx, need_db);
         variable_list out;
         for (const py::handle& t : py::reinterpret_borrow<py::tuple>(r))
             out.push_back(t.is_none() ? Tensor() : t.cast<Tensor>());
