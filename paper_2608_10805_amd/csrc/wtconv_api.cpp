@@ -1528,33 +1528,42 @@ double rounds_fill(long B, long groups, int nchunks, int nb, int wgs)
     return (double)B * groups / ((double)((grid + slots - 1) / slots) * slots * nb);
 }
 
-// float32 region tiles against the vector kernels' 56 x 56 ones. With a carry
-// (phase_f32_tiles_pay()) only the rounds' fill is left to ask for (polyphase /
-// vector training step, fills in brackets): 69 x 102 B18 C136 (0.53, 0.64) 1.05, 60
-// x 170 C64 B1 (0.25, 0.5) 1.04, 169 x 169 B1 C64 k3 (0.50, 1.0) 1.05; 128 x 128 B2
-// C64 k3 (0.50, 0.56) 0.97, 113 x 113 B9 C70 (0.74) 0.88. At L = 1, polyphase /
-// vector forward by the padded areas' ratio times the fill: one or two planes per
-// tile do not make up for its weight tables below 1 (k = 5: 224 x 224 B1 C144 0.75
-// 1.15, 112 x 112 B1 C144 0.56 1.05, 148 x 148 B1 C144 0.59 1.10; 320 x 320 B1 C96
-// 1.05 1.02; 80 x 120 B4 C64 1.8 0.68), at k = 3 below 0.78 (224 x 224 B1 0.75 1.08,
-// 168 x 168 B1 C64 0.44 1.21; 148 x 148 B1 0.79 0.93); from three on 0.65 will do
-// (224 x 224 B4 k5 0.75 0.94; k3 B8 C64 0.67 0.88) where the tiles pad no more than
-// the vector ones (168 x 168, 1.14 and 1.0: k5 B8 C64 1.14, k3 B16 C96 1.23, k3 B26
-// C40 step 1.07).
+// float32 region tiles against the vector kernels' 56 x 56 ones, by the padded
+// areas' ratio times how full the polyphase tiles' rounds are ("share").
+// With a carry (phase_f32_tiles_pay()), polyphase / vector training step: 119 x 119
+// B128 C144 k3 1.10 0.87, 88 x 116 B64 C144 0.86 0.92, 169 x 169 B8 C64 1.09 0.96;
+// 69 x 102 B18 C136 0.82 1.05, 60 x 170 B1 C64 0.59 1.04, 169 x 169 B1 k3 0.73 1.05;
+// down to 0.75 where the vector tiles' rounds are no fuller (128 x 128 B2 C64 k3
+// 0.77 0.97). At L = 1, polyphase / vector forward: one or two planes per tile do
+// not make up for its weight tables below 1 (k = 5: 224 x 224 B1 C144 0.75 1.15, 112
+// x 112 B1 C144 0.56 1.05, 148 x 148 B1 C144 0.59 1.10; 320 x 320 B1 C96 1.05 1.02; 80
+// x 120 B4 C64 1.8 0.68), at k = 3 below 0.78 (224 x 224 B1 0.75 1.08, 168 x 168 B1
+// C64 0.44 1.21; 148 x 148 B1 0.79 0.93); from three on 0.7 will do (224 x 224 B4
+// 0.75 0.94; 209 x 256 B32 C32 0.65 1.06, 147 x 147 B32 C144 0.59 1.05), 0.6 at k = 3
+// (99 x 99 B48 C435 0.61 0.72, 278 x 185 B32 C48 0.64 0.85), where the tiles pad at
+// most a tenth more than the vector ones (168 x 168 1.14: k5 B8 C64 1.14, k3 B16 C96
+// 1.23; 218 x 277 k3 1.1: 0.95). Strips of up to 40 columns lose in more than two
+// rounds, where a strip's neighbours, which read its halo columns again, need not
+// run beside it (171 x 171 B8 C512 k3 L2 training step 1.10, 169 x 169 B12 C512 L2
+// 1.10, 165 x 165 B4 C384 L1 1.14; in one round 170 x 170 B200 C24 L3 0.89; tiles of
+// 72 columns in eight 266 x 68 B16 C768 L2 0.81).
 bool phase_f32_region_pays(const wtconv_desc& d, const PhasePlan& pl, bool carry)
 {
     const wtc::PhaseArgs& a = pl.a;
     const int tiles = a.rg_ntx * a.rg_nty;
-    const double fill = rounds_fill(d.B, (long)d.C * tiles, pl.nchunks, a.nb, phase_wgs(d, a, 2));
+    const double vec = 56.0 * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
+    const double pad = vec / ((double)tiles * a.rg_th * a.rg_tw);
+    const int wgs = phase_wgs(d, a, 2);
+    if (a.rg_tw <= 40 && (long)pl.nchunks * d.C * tiles > 512L * wgs) return false;
+    const double fill = rounds_fill(d.B, (long)d.C * tiles, pl.nchunks, a.nb, wgs);
+    const double share = pad * fill;
     if (carry) {
         const RegionPlan rp = choose(d, false).rp;
         const double vec_fill = rounds_fill(d.B, (long)d.C * rp.ntx * rp.nty, rp.pl.nchunks, rp.pl.nb, 4);
-        return fill >= 0.6 || (fill >= 0.5 && fill >= 0.85 * vec_fill);
+        return share >= 0.85 || (share >= 0.75 && fill >= 0.85 * vec_fill);
     }
-    const double vec = 56.0 * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
-    const double pad = vec / ((double)tiles * a.rg_th * a.rg_tw);
-    if (a.nb >= 3 && pad >= 0.95) return pad * fill >= 0.65;
-    return pad >= 1.03 && pad * fill >= (d.k == 3 ? 0.78 : 1.0);
+    if (a.nb >= 3 && pad >= 0.9) return share >= (d.k == 3 ? 0.6 : 0.7);
+    return pad >= 1.03 && share >= (d.k == 3 ? 0.78 : 1.0);
 }
 
 // Lane-cycles per plane of the two forwards as their planners model them,
@@ -1570,27 +1579,32 @@ double phase_model_ratio(const wtconv_desc& d, const wtc::PhaseArgs& a, int roun
     return phase_cycles(d, a, rounds) / a.PP / phase_wgs(d, a, rounds) / issue * (mixed || pl.one_round ? 1.0 : 0.75);
 }
 
-// float32, L = 1, both kernels over whole planes: the model ratio with each side's
-// fill of its rounds. The general vector variant is always the slower one.
-// Polyphase / vector forward by that figure: one round k = 5 0.23 (64 x 64 B64 C96)
-// 0.90, 0.34 (40 x 40 B64 C128) 0.94, 0.42 and 0.47 (56 x 56 and 64 x 64 B16 C64)
-// 1.03 and 1.09; k = 3 0.55 0.87-0.97, 0.75 (40 x 40 B64 C128) 0.93, 0.82 (56 x 56
-// B16 C128) 1.05, 0.96 (64 x 64 B16 C64) 1.13; two rounds mixed in one launch k = 5
-// 0.22 (12 x 16) 0.78, 0.35 (16 x 16 B64 C96) 1.07, 0.51 (B64 C256) 1.11; k = 3 0.66
-// 0.94-1.0, 0.81 0.99 (step 1.10-1.15), 1.09 1.02-1.08; eight batches of planes and
-// more make up for it there (14 x 12 B128 C435 0.46 and 0.97: 0.84, 0.75).
+// float32, L = 1, both kernels over whole planes. The general vector variant is
+// always the slower one. Against one round of blocks, four batches of planes per
+// workgroup make up for the weight tables (polyphase / vector training step 63 x 63
+// B8 C512 0.97, 62 x 18 B32 C512 0.83, 34 x 33 B256 C512 k3 0.81; 15 x 66 B24 C435
+// 1.02), against two rounds mixed in one launch eight (14 x 12 B128 C435 0.93, k3
+// 0.88). With fewer it is the model ratio with each side's fill of its rounds: one
+// round k = 5 0.23 (64 x 64 B64 C96) 0.95, 0.34 (40 x 40 B64 C128) 0.98, 0.42 and 0.47
+// (56 x 56 and 64 x 64 B16 C64) 1.03 and 1.06; k = 3 0.55 0.92-0.98, 0.82 (56 x 56 B16
+// C128) 1.05, 0.96 (64 x 64 B16 C64) 1.11; mixed, one batch k = 5 0.22 (12 x 16) 0.88,
+// 0.35 (16 x 16 B64 C96) 1.09; k = 3 0.66 0.95-1.0, 0.81 1.10-1.15; two and three
+// batches k = 5 0.38 (13 x 13 B100 C256) 0.91, 0.51 (16 x 16 B64 C256) 1.09; k = 3 0.73
+// (13 x 13 B48 C384) 0.91, 0.82 (14 x 14 B128 C256) 0.96, 1.09 (16 x 16) 1.03.
 bool phase_f32_one_level_pays(const wtconv_desc& d, const PhasePlan& pp, const Exec& ex)
 {
     const Plan& pl = ex.pl;
     const bool mixed = pl.mx.rounds > 0;
     if (!mixed && !pl.one_round) return true;
-    if (mixed && pp.a.nb >= 8 * pp.a.PP) return true;
+    if (pp.a.nb >= (mixed ? 8 : 4) * pp.a.PP) return true;
     double busy;
-    const int wgs = std::min(4, mixed ? lds_wgs(pl.lds_floats) : std::min(forward_wgs(d, true), lds_wgs(pl.lds_floats)));
+    const int lds = std::min(4, lds_wgs(pl.lds_floats));
+    const int wgs = mixed ? lds : std::min(forward_wgs(d, true), lds);
     const double fill = rounds_fill(d.B, d.C, pl.nchunks, pl.nb, wgs);
     const double ratio = phase_model_ratio(d, pp.a, pp.rounds, ex, busy) * fill /
                          rounds_fill(d.B, d.C, pp.nchunks, pp.a.nb, phase_wgs(d, pp.a, pp.rounds));
-    return ratio <= (mixed ? (d.k == 3 ? 0.7 : 0.3) : (d.k == 3 ? 0.75 : 0.4));
+    if (!mixed) return ratio <= (d.k == 3 ? 0.75 : 0.4);
+    return pp.a.nb > pp.a.PP ? ratio <= (d.k == 3 ? 0.85 : 0.4) : ratio <= (d.k == 3 ? 0.7 : 0.3);
 }
 
 // Where the polyphase forward is the faster one. Measured on MI355X against the
@@ -1603,24 +1617,29 @@ bool phase_f32_one_level_pays(const wtconv_desc& d, const PhasePlan& pp, const E
 //    to 1.3 0.99-1.40 (48 x 48), 2.0 0.99-1.005, 8 0.89-0.96; 16 bits at L >= 4
 //    0.1 to 1.3 1.00-1.15 (56 x 56, 64 x 64, 28 x 28), 2.0 0.93-1.02, 4 0.85-0.95;
 //    float16 at L2-L3 0.5 (64 x 64) 1.02-1.05, 0.7 0.96-1.02, 1.3 0.98-0.99;
-//  - float32, L = 2 and 3: nothing is gained where fewer planes per CU are
-//    resident than in the vector plan, up to three (training step, 64 x 64 k3 L3
-//    1.16; 72 x 72 k3 L2 1.29, k5 L3 1.27; 50 x 70 k3 L3 1.09);
-//  - then at k = 5 the matrix instructions take as long as the vector kernels'
+//  - float32, L = 2 and 3, k = 3: nothing is gained where fewer planes per CU are
+//    resident than in the vector plan, up to three (training step, 64 x 64 L3 1.16;
+//    72 x 72 L2 1.29; 50 x 70 L3 1.09);
+//  - at k = 5 the matrix instructions take as long as the vector kernels'
 //    FMAs where these have their lanes full (56 x 56 L2 0.95 to 1.007 by card, L3
 //    0.96 to 1.05; 64 x 64 L2 0.98 to 1.02; 40 x 40 L2 0.98 to 1.04), less where a
 //    quarter or more of the 4 x 4 blocks' lanes idle (48 x 48 0.90; 63 x 95 0.78,
-//    0.81; 47 x 61 0.95 to 1.006, 0.98) or three workgroups per CU with 30 % of
-//    their lanes idle (60 x 60 L2 0.87; 55 x 57 L3 0.91; 32 x 32 L3 0.90; 44 x 44
-//    0.95, 0.94), while the model gives it half of the vector kernels' time (28 x
-//    28 0.51 and 0.59: 0.99; 31 x 47 L3 0.61: 1.11), and on the smallest planes at
-//    L = 2 (20 x 20 0.97, 14 x 14 0.96) if the last round is not half empty (14 x 12
-//    B128 C435, 435 workgroups in 768 places: 1.05);
-//  - at k = 3 where the model ratio is at most 1.4 (28 x 28 L3 1.26: 0.99; 24 x 24
+//    0.81; 65 x 65 L2 0.78; 47 x 61 0.95 to 1.006, 0.98) or three workgroups per CU with 30 % of
+//    their lanes idle (60 x 60 L2 0.87; 55 x 57 L3 0.91; 32 x 32 L3 0.90),
+//    while the model gives it half of the vector kernels' time (28 x 28 0.51 and
+//    0.59: 0.99; 31 x 47 L3 0.61: 1.11; 72 x 72 L3 0.93: 1.27), below eight batches
+//    also with both fills (30 x 25 B24 C96 L3 0.61: 1.11), and on the smallest
+//    planes at L = 2 (20 x 20 0.97, 14 x 14 0.96) from three batches on (14 x 14 C256
+//    B64 0.90; one and two: 14 x 14 B64 C96 1.10, 10 x 10 B24 C384 1.17, 20 x 20 B36
+//    C110 1.09), if the rounds are four fifths full (14 x 12 B128 C435 0.57: 1.05; 14 x 14 B128 C300 0.78: 1.03; 17 x 17 B200 C512
+//    0.67, ratio 0.40: 0.90);
+//  - then at k = 3 where the model ratio is at most 1.4 (28 x 28 L3 1.26: 0.99; 24 x 24
 //    L2 1.33: 0.90; 35 x 90 L3 1.46: 1.08), 0.95 if the vector lanes are 75 % full
 //    (40 x 40 L2 0.91: 0.96; 32 x 32 L2 1.01 and L3 1.26: 1.01-1.04) and 0.9 at 80 %
 //    (55 x 57 L3 0.90: 0.99; 35 x 90 L2 0.91 and 50 x 70 L2 1.2: 1.03); at L3 with
-//    one round of blocks (two spill: 72 x 72 1.14);
+//    one round of blocks (two spill: 72 x 72 1.14); against two rounds mixed in one
+//    launch from eight batches on (14 x 14 L2 B128 C384 0.995, B64 C256 three 1.04,
+//    B64 C96 one 1.11);
 //  - float32, L >= 4: 0.84 to 1.8 (its deeper stages need six products per
 //    term and one wavefront runs them);
 //  - 16-bit, L = 5: 56 x 56 0.88, 28 x 28 0.75, 20 x 20 0.78, but 40 x 40 1.08
@@ -1652,16 +1671,20 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
         if (d.L > 3 || (ex.mode != Mode::Resident && ex.mode != Mode::Split)) return false;
         const Plan& pl = ex.pl;
         const int wgs = std::min(forward_wgs(d, pl.one_round != 0), lds_wgs(pl.lds_floats));
-        if (a.PP * phase_wgs(d, a, e.pl.rounds) < std::min(3, pl.PP * wgs)) return false;
+        if (d.k == 3 && a.PP * phase_wgs(d, a, e.pl.rounds) < std::min(3, pl.PP * wgs)) return false;
         double busy;
         const double ratio = phase_model_ratio(d, a, e.pl.rounds, ex, busy);
         if (d.k == 3)
-            return (d.L == 2 || e.pl.rounds == 1) && ratio <= (busy >= 0.8 ? 0.9 : (busy >= 0.75 ? 0.95 : 1.4));
+            return (d.L == 2 || e.pl.rounds == 1) && (pl.mx.rounds == 0 || a.nb >= 8 * a.PP) &&
+                   ratio <= (busy >= 0.8 ? 0.9 : (busy >= 0.75 ? 0.95 : 1.4));
         const int blocks = a.bx * a.by, lanes = ceil_to(blocks, wtc::kThreads);
         const int used = blocks <= wtc::kThreads ? wtc::kThreads / blocks * blocks : blocks;
         const bool idle = 4 * used <= 3 * lanes || (wgs <= 3 && busy <= 0.7);
         const double fill = rounds_fill(d.B, d.C, e.pl.nchunks, a.nb, phase_wgs(d, a, e.pl.rounds));
-        return (d.L == 2 && edge <= 20 && (fill >= 0.8 || a.nb <= 3 * a.PP)) || (idle && ratio <= 0.5);
+        const bool filled = a.nb >= 3 * a.PP && (fill >= 0.8 || (fill >= 0.65 && ratio <= 0.41));
+        const double vec_fill = rounds_fill(d.B, d.C, pl.nchunks, pl.nb, std::min(4, wgs));
+        const bool half = ratio <= 0.5 && (a.nb >= 8 * a.PP || ratio * vec_fill <= 0.55 * fill);
+        return (d.L == 2 && edge <= 20 && filled) || (idle && half);
     }
     if (d.L <= 4) return true;
     return edge >= 48 || (edge <= 32 && (long)d.B * d.C < kPhaseSmallL5Planes);

@@ -226,7 +226,10 @@ def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
     ((8, 64, 60, 170, 5, 3, "f32"), 2), ((16, 64, 224, 224, 5, 3, "f32"), 0), ((16, 64, 100, 100, 5, 2, "f32"), 0),
     ((16, 96, 72, 72, 5, 4, "f32"), 0), ((16, 64, 224, 224, 5, 3, "bf16"), 2),
     ((18, 136, 69, 102, 5, 3, "f32"), 0), ((1, 64, 169, 169, 3, 2, "f32"), 0), ((2, 64, 128, 128, 3, 2, "f32"), 2),
+    ((128, 144, 119, 119, 3, 3, "f32"), 2), ((8, 512, 171, 171, 3, 2, "f32"), 0), ((16, 768, 266, 68, 5, 2, "f32"), 2),
     # float32, L = 1
+    ((8, 512, 63, 63, 5, 1, "f32"), 1), ((100, 256, 13, 13, 5, 1, "f32"), 1), ((64, 256, 16, 16, 5, 1, "f32"), 0),
+    ((48, 435, 99, 99, 3, 1, "f32"), 2), ((16, 96, 111, 155, 5, 1, "f32"), 0),
     ((1, 144, 224, 224, 5, 1, "f32"), 0), ((4, 144, 224, 224, 5, 1, "f32"), 2), ((1, 144, 148, 148, 5, 1, "f32"), 0),
     ((1, 144, 148, 148, 3, 1, "f32"), 2), ((26, 40, 168, 168, 3, 1, "f32"), 0), ((4, 64, 80, 120, 5, 1, "f32"), 2),
     ((16, 64, 64, 64, 5, 1, "f32"), 0), ((64, 96, 64, 64, 5, 1, "f32"), 1), ((16, 64, 56, 56, 3, 1, "f32"), 0),
@@ -242,7 +245,10 @@ def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
     ((64, 96, 56, 56, 5, 3, "f32"), 0), ((64, 96, 48, 48, 5, 3, "f32"), 1), ((32, 128, 55, 57, 5, 3, "f32"), 1),
     ((64, 96, 60, 60, 5, 2, "f32"), 1), ((64, 192, 28, 28, 5, 3, "f32"), 0), ((32, 128, 63, 95, 5, 3, "f32"), 1),
     ((64, 256, 20, 20, 5, 2, "f32"), 1), ((64, 256, 20, 20, 5, 3, "f32"), 0),
-    ((128, 384, 14, 14, 5, 2, "f32"), 1), ((128, 435, 14, 12, 5, 2, "f32"), 0),
+    ((128, 384, 14, 14, 5, 2, "f32"), 1), ((128, 435, 14, 12, 5, 2, "f32"), 0), ((200, 512, 17, 17, 5, 2, "f32"), 1),
+    ((100, 64, 65, 65, 5, 2, "f32"), 1), ((48, 435, 65, 65, 3, 2, "f32"), 0),
+    ((24, 96, 30, 25, 5, 3, "f32"), 0), ((100, 48, 30, 30, 5, 3, "f32"), 1),
+    ((64, 96, 14, 14, 5, 2, "f32"), 0), ((64, 256, 14, 14, 5, 2, "f32"), 1), ((64, 256, 14, 14, 3, 2, "f32"), 0),
     # float32, k = 3
     ((64, 192, 28, 28, 3, 3, "f32"), 1), ((64, 192, 32, 32, 3, 2, "f32"), 0), ((32, 128, 35, 90, 3, 2, "f32"), 0),
     ((64, 128, 40, 40, 3, 2, "f32"), 1), ((32, 128, 55, 57, 3, 3, "f32"), 1), ((32, 128, 63, 95, 3, 3, "f32"), 0)])
