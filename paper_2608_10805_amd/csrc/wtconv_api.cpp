@@ -1542,11 +1542,12 @@ double rounds_fill(long B, long groups, int nchunks, int nb, int wgs)
 // 0.75 0.94; 209 x 256 B32 C32 0.65 1.06, 147 x 147 B32 C144 0.59 1.05), 0.6 at k = 3
 // (99 x 99 B48 C435 0.61 0.72, 278 x 185 B32 C48 0.64 0.85), where the tiles pad at
 // most a tenth more than the vector ones (168 x 168 1.14: k5 B8 C64 1.14, k3 B16 C96
-// 1.23; 218 x 277 k3 1.1: 0.95). Strips of up to 40 columns lose in more than two
+// 1.23; 218 x 277 k3 1.1: 0.95). Four strips of 32 columns and more lose after three
 // rounds, where a strip's neighbours, which read its halo columns again, need not
-// run beside it (171 x 171 B8 C512 k3 L2 training step 1.10, 169 x 169 B12 C512 L2
-// 1.10, 165 x 165 B4 C384 L1 1.14; in one round 170 x 170 B200 C24 L3 0.89; tiles of
-// 72 columns in eight 266 x 68 B16 C768 L2 0.81).
+// run beside it (training step 171 x 171 B8 C512 k3 L2 1.10, 175 x 117 B16 C512 L2
+// 1.07, 165 x 165 B4 C384 L1 1.14; in three rounds 171 x 171 B8 C256 L2 0.93; two
+// strips in three rounds 167 x 64 B8 C768 L3 0.91, three of 40 columns in more 113 x
+// 113 B8 C768 L3 0.91).
 bool phase_f32_region_pays(const wtconv_desc& d, const PhasePlan& pl, bool carry)
 {
     const wtc::PhaseArgs& a = pl.a;
@@ -1554,7 +1555,7 @@ bool phase_f32_region_pays(const wtconv_desc& d, const PhasePlan& pl, bool carry
     const double vec = 56.0 * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
     const double pad = vec / ((double)tiles * a.rg_th * a.rg_tw);
     const int wgs = phase_wgs(d, a, 2);
-    if (a.rg_tw <= 40 && (long)pl.nchunks * d.C * tiles > 512L * wgs) return false;
+    if (a.rg_tw <= 32 && a.rg_ntx >= 4 && (long)pl.nchunks * d.C * tiles > 768L * wgs) return false;
     const double fill = rounds_fill(d.B, (long)d.C * tiles, pl.nchunks, a.nb, wgs);
     const double share = pad * fill;
     if (carry) {
