@@ -1528,6 +1528,25 @@ double rounds_fill(long B, long groups, int nchunks, int nb, int wgs)
     return (double)B * groups / ((double)((grid + slots - 1) / slots) * slots * nb);
 }
 
+// Four strips of 32 columns and more, after three rounds of workgroups: a strip's
+// neighbours, which read its halo columns again, need not run beside it. Polyphase
+// / vector training step, float32: 171 x 171 B8 C512 k3 L2 1.10, 175 x 117 B16 C512
+// L2 1.07, 165 x 165 B4 C384 L1 1.14; in three rounds 171 x 171 B8 C256 L2 0.93; two
+// strips in three rounds 167 x 64 B8 C768 L3 0.91, three of 40 columns in more 113 x
+// 113 B8 C768 L3 0.91. In 16 bits only where they also pad more than the vector
+// tiles and the tensor is larger than the 256 MB last-level cache: bf16 164 x 164
+// L1 B12 C768 (496 MB) 1.37, B12 C512 (330 MB) 1.20, B4 C768 (165 MB) 0.91, B4 C384
+// 0.79; padding less 171 x 171 B12 C768 0.87, 192 x 192 B8 C768 0.77.
+bool phase_strips_lose(const wtconv_desc& d, const PhasePlan& pl)
+{
+    const wtc::PhaseArgs& a = pl.a;
+    const int tiles = a.rg_ntx * a.rg_nty;
+    if (a.rg_tw > 32 || a.rg_ntx < 4 || (long)pl.nchunks * d.C * tiles <= 768L * phase_wgs(d, a, 2)) return false;
+    if (d.dtype == WTCONV_F32) return true;
+    const long vec = 56L * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
+    return vec < (long)tiles * a.rg_th * a.rg_tw && 2L * d.B * d.C * d.H * d.W > 1L << 28;
+}
+
 // float32 region tiles against the vector kernels' 56 x 56 ones, by the padded
 // areas' ratio times how full the polyphase tiles' rounds are ("share").
 // With a carry (phase_f32_tiles_pay()), polyphase / vector training step: 119 x 119
@@ -1542,21 +1561,14 @@ double rounds_fill(long B, long groups, int nchunks, int nb, int wgs)
 // 0.75 0.94; 209 x 256 B32 C32 0.65 1.06, 147 x 147 B32 C144 0.59 1.05), 0.6 at k = 3
 // (99 x 99 B48 C435 0.61 0.72, 278 x 185 B32 C48 0.64 0.85), where the tiles pad at
 // most a tenth more than the vector ones (168 x 168 1.14: k5 B8 C64 1.14, k3 B16 C96
-// 1.23; 218 x 277 k3 1.1: 0.95). Four strips of 32 columns and more lose after three
-// rounds, where a strip's neighbours, which read its halo columns again, need not
-// run beside it (training step 171 x 171 B8 C512 k3 L2 1.10, 175 x 117 B16 C512 L2
-// 1.07, 165 x 165 B4 C384 L1 1.14; in three rounds 171 x 171 B8 C256 L2 0.93; two
-// strips in three rounds 167 x 64 B8 C768 L3 0.91, three of 40 columns in more 113 x
-// 113 B8 C768 L3 0.91).
+// 1.23; 218 x 277 k3 1.1: 0.95).
 bool phase_f32_region_pays(const wtconv_desc& d, const PhasePlan& pl, bool carry)
 {
     const wtc::PhaseArgs& a = pl.a;
     const int tiles = a.rg_ntx * a.rg_nty;
     const double vec = 56.0 * 56 * cdiv(d.H, 56) * cdiv(d.W, 56);
     const double pad = vec / ((double)tiles * a.rg_th * a.rg_tw);
-    const int wgs = phase_wgs(d, a, 2);
-    if (a.rg_tw <= 32 && a.rg_ntx >= 4 && (long)pl.nchunks * d.C * tiles > 768L * wgs) return false;
-    const double fill = rounds_fill(d.B, (long)d.C * tiles, pl.nchunks, a.nb, wgs);
+    const double fill = rounds_fill(d.B, (long)d.C * tiles, pl.nchunks, a.nb, phase_wgs(d, a, 2));
     const double share = pad * fill;
     if (carry) {
         const RegionPlan rp = choose(d, false).rp;
@@ -1659,7 +1671,7 @@ bool phase_pays(const wtconv_desc& d, const PhaseExec& e)
     const int edge = std::max(d.H, d.W);
     const Exec ex = choose(d, false);
     if (e.kind == PhaseExec::Region)
-        return ex.mode == Mode::Region && (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d)) &&
+        return ex.mode == Mode::Region && !phase_strips_lose(d, e.pl) && (d.dtype != WTCONV_F32 || d.L < 2 || phase_f32_tiles_pay(d)) &&
                (d.dtype != WTCONV_F32 || phase_f32_region_pays(d, e.pl, d.L >= 2));
     const wtc::PhaseArgs& a = e.pl.a;
     const bool f32 = d.dtype == WTCONV_F32;
@@ -1713,9 +1725,9 @@ PhaseExec choose_phase(const wtconv_desc& d, int skip_base, bool region = false)
             e.kind = PhaseExec::Resident;
         else if (make_phase_region_plan(d, e.pl))
             e.kind = PhaseExec::Region;
-        if (region)
-            return d.dtype != WTCONV_F32 || phase_f32_region_pays(d, e.pl, true) ? e : none;
-        return phase_pays(d, e) ? e : none;
+        if (!region) return phase_pays(d, e) ? e : none;
+        if (e.kind == PhaseExec::None || phase_strips_lose(d, e.pl)) return none;
+        return d.dtype != WTCONV_F32 || phase_f32_region_pays(d, e.pl, true) ? e : none;
     });
 }
 

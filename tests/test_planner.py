@@ -228,6 +228,7 @@ def test_where_the_gradient_pass_is_polyphase(phase_routes, spec, phase):
     ((18, 136, 69, 102, 5, 3, "f32"), 0), ((1, 64, 169, 169, 3, 2, "f32"), 0), ((2, 64, 128, 128, 3, 2, "f32"), 2),
     ((128, 144, 119, 119, 3, 3, "f32"), 2), ((8, 512, 171, 171, 3, 2, "f32"), 0), ((16, 768, 266, 68, 5, 2, "f32"), 2),
     ((8, 256, 171, 171, 5, 2, "f32"), 2), ((8, 768, 113, 113, 5, 3, "f32"), 2),
+    ((12, 768, 164, 164, 5, 1, "bf16"), 0), ((4, 768, 164, 164, 5, 1, "bf16"), 2), ((12, 768, 171, 171, 3, 1, "f16"), 2),
     # float32, L = 1
     ((8, 512, 63, 63, 5, 1, "f32"), 1), ((100, 256, 13, 13, 5, 1, "f32"), 1), ((64, 256, 16, 16, 5, 1, "f32"), 0),
     ((48, 435, 99, 99, 3, 1, "f32"), 2), ((16, 96, 111, 155, 5, 1, "f32"), 0),
